@@ -23,67 +23,14 @@
 
 #include <type_traits>
 
-#include "nt_common.h"
-#include "nt_kernels.h"
+#include "nt_gemm_common.h"
 
 namespace nt {
 namespace {
 
 constexpr int BM = 128, BN = 128;
-constexpr int ROWB = 128;           // bytes of K per tile row per step
 constexpr int CH = ROWB / 16;       // 16-byte chunks per tile row
 constexpr int NTHR = 256;
-
-// Byte offset of 16-byte chunk `ch` of tile row `row` in a swizzled LDS tile.
-__device__ __forceinline__ int swz(int row, int ch) { return row * ROWB + ((ch ^ (row & 7)) << 4); }
-// Same for the 64-byte rows of an FP8 weight tile (64 k-values per step): rows r, r+4,
-// r+8, r+12 fall on the same banks, so the chunk position is XORed with bits 2..3 of
-// the row and 16 consecutive rows read at one chunk hit 16 distinct bank groups.
-constexpr int ROWB8 = 64;
-__device__ __forceinline__ int swz8(int row, int ch) { return row * ROWB8 + ((ch ^ ((row >> 2) & 3)) << 4); }
-
-// Eight FP8 E4M3 weights (two 32-bit words, k in byte order) as eight fp16 values of an
-// MFMA operand.  Every E4M3 value is exact in fp16, so the conversion loses nothing.
-template <bool HI>
-__device__ __forceinline__ unsigned f8x2(unsigned w) {
-  return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w, 1.0f, HI));
-}
-__device__ __forceinline__ u32x4 f8_to_f16x8(unsigned w0, unsigned w1) {
-  return u32x4{f8x2<false>(w0), f8x2<true>(w0), f8x2<false>(w1), f8x2<true>(w1)};
-}
-
-// Sum and sum of squares of the eight (fp16/bf16) or four (fp32) values of one 16-byte
-// operand fragment, each taken relative to the row's shift c (one of the row's own
-// values), added into s and q in fp32: the row statistics of a folded LayerNorm.  With
-// the shift, the variance (q/K - (s/K)^2) no longer cancels when the row's mean is large
-// against its spread: the deviations from c are of the size of the spread.  For fp16 the
-// deviation is formed in fp16 (exact whenever x and c are within a factor of two, which is
-// where cancellation would matter), then squared and summed by fdot2 in fp32.
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ void frag_stats(const u32x4& a, T c, float& s, float& q) {
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if constexpr (std::is_same<T, f16>::value) {
-      // the word is copied out first: a bit_cast of the vector element itself read word 0
-      const unsigned u = a[w];
-      const half2v h = __builtin_bit_cast(half2v, u) - half2v{c, c};
-      s = __builtin_amdgcn_fdot2(h, half2v{(_Float16)1.0f, (_Float16)1.0f}, s, false);
-      q = __builtin_amdgcn_fdot2(h, h, q, false);
-    } else if constexpr (std::is_same<T, bf16>::value) {
-      const float cf = to_f32(c);
-      const float lo = __uint_as_float(a[w] << 16) - cf, hi = __uint_as_float(a[w] & 0xffff0000u) - cf;
-      s += lo;
-      s += hi;
-      q = fmaf(lo, lo, q);
-      q = fmaf(hi, hi, q);
-    } else {
-      const float x = __uint_as_float(a[w]) - to_f32(c);
-      s += x;
-      q = fmaf(x, x, q);
-    }
-  }
-}
 
 // Four consecutive elements of the model dtype as loaded (raw bits: converted only where
 // they are used, so the load does not have to complete where it is issued).
@@ -101,109 +48,6 @@ __device__ __forceinline__ float4 raw4_to_f32(typename Raw4<T>::type r) {
     return make_float4(to_f32(h[0]), to_f32(h[1]), to_f32(h[2]), to_f32(h[3]));
   }
 }
-
-// Applies the epilogue MODE to up to 4 consecutive columns n..n+3 of row m (n % 4 == 0).
-// With OPS, it adds the bias (if any) and, for EPI_RESID, the residual itself; without,
-// the caller has added both (an EPI_RESID group is then a plain store).  The mode is a
-// template argument so that a tile's unrolled groups carry only their own mode's code.
-// fp32 output (out_f32) goes with EPI_STORE only.  d, dh and ldc are multiples of 4 in
-// every mode that scatters, so the 4 columns never straddle a head or a K/V boundary and
-// land on 4 consecutive destination elements.
-template <typename T, int MODE, bool OPS>
-__device__ __forceinline__ void epilogue4(const GemmEpi& e, int m, int n, int N, float4 v4, int t_slot) {
-  float v[4] = {v4.x, v4.y, v4.z, v4.w};
-  const int cnt = min(4, N - n);
-  if constexpr (OPS) {
-    if (e.bias) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (k < cnt) v[k] += e.bias[n + k];
-    }
-  }
-  const bool vec = cnt == 4 && (e.ldc & 3) == 0;
-  if constexpr (MODE == EPI_STORE) {
-    if (e.out_f32) {
-      const int mo = e.out_map ? e.sent_list[m / e.beam] * e.beam + m % e.beam : m;
-      float* o = static_cast<float*>(e.out) + (size_t)mo * e.ldc + n;
-      if (vec) {
-        *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (k < cnt) o[k] = v[k];
-      }
-      return;
-    }
-  }
-  T* o = nullptr;
-  if constexpr (MODE == EPI_STORE) {
-    o = static_cast<T*>(e.out) + (size_t)m * e.ldc + n;
-  } else if constexpr (MODE == EPI_RELU) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = fmaxf(v[k], 0.f);
-    o = static_cast<T*>(e.out) + (size_t)m * e.ldc + n;
-  } else if constexpr (MODE == EPI_RESID) {
-    if constexpr (OPS) {
-      const T* r = static_cast<const T*>(e.resid) + (size_t)m * e.ldc + n;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (k < cnt) v[k] += to_f32(r[k]);
-    }
-    o = static_cast<T*>(e.out) + (size_t)m * e.ldc + n;
-  } else if constexpr (MODE == EPI_SELF_QKV) {
-    if (n < e.d) {
-      o = static_cast<T*>(e.out) + (size_t)m * e.ldc + n;
-    } else {
-      int c = n - e.d;
-      const int kv = c >= e.d;
-      c -= kv * e.d;
-      const int h = c / e.dh, x = c - h * e.dh;
-      const int p = e.sent_list[m / e.beam] * e.beam + m % e.beam;
-      const size_t idx = ((size_t)(p * e.H + h) * e.Tcap + t_slot) * e.dh + x;
-      if (e.kv_f8) {   // E4M3 cache: the 4 columns as 4 bytes, one 32-bit store (idx % 4 == 0)
-        uint8_t* o8 = static_cast<uint8_t*>(kv ? e.vcache : e.kcache) + idx;
-        if (cnt == 4) {
-          *reinterpret_cast<uint32_t*>(o8) = (uint32_t)e4m3_rne(v[0]) | ((uint32_t)e4m3_rne(v[1]) << 8) |
-                                             ((uint32_t)e4m3_rne(v[2]) << 16) | ((uint32_t)e4m3_rne(v[3]) << 24);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (k < cnt) o8[k] = e4m3_rne(v[k]);
-        }
-        return;
-      }
-      o = static_cast<T*>(kv ? e.vcache : e.kcache) + idx;
-    }
-  } else {
-    static_assert(MODE == EPI_CROSS_KV, "epilogue mode");
-    const int j = n / (2 * e.d);
-    int c = n - j * 2 * e.d;
-    const int kv = c >= e.d;
-    c -= kv * e.d;
-    const int h = c / e.dh, x = c - h * e.dh;
-    const int b = m / e.S, s = m - b * e.S;
-    o = static_cast<T*>(e.cross) + ((((size_t)j * 2 + kv) * e.B + b) * e.H + h) * (size_t)e.S * e.dh +
-        (size_t)s * e.dh + x;
-  }
-  if (vec || (MODE >= EPI_SELF_QKV && cnt == 4)) {
-    if constexpr (sizeof(T) == 2) {
-      T t4[4] = {from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
-      *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(t4);
-    } else {
-      *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k < cnt) o[k] = from_f32<T>(v[k]);
-  }
-}
-
-// s_waitcnt immediate that waits until at most `vm` vector-memory operations of this wave
-// are outstanding (expcnt / lgkmcnt left unconstrained).
-__host__ __device__ constexpr int vmcnt_imm(int vm) { return (vm & 0xF) | ((vm >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
-
-#define NT_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
 // Fragment reads are issued as inline ds_read_b128 so that the compiler does not place a
 // wait for every in-flight direct global->LDS load in front of them (it cannot tell them
@@ -870,11 +714,56 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
   return hipErrorInvalidValue;
 }
 
+// Rows (and, but for 64, columns) of the phased tile a product runs on, or 0 for the tiles of
+// this file.  Both give the same bits.  Measured on MI355X, launches of one shape replayed
+// back to back from a graph (us, this file's tile against the phased one):
+//  * K in whole pairs of 64 (an even number of k-steps), 16-bit activations, and operands
+//    within 32-bit byte offsets are what the phased kernel takes.
+//  * The output projection always (16x32000x512 12.6 / 8.5, 1300x32000x512 78 / 52).
+//  * Else by the number of 64x128 tiles (T64), a CU's worth of work each.  Few tiles leave most
+//    CUs idle, and the 64x32 tiles below, four times as many, finish first: 1500x512x512 (96
+//    tiles) 5.5 / 6.3, 800x1024x4096 (104) 20.8 / 24.1; from 112 on the phased tile wins:
+//    1114x1024x4096 (144) 38.3 / 24.5, 700x1536x512 (132) 7.7 / 6.2.  With a folded LayerNorm
+//    the line lies at 64 tiles: 400x1024x1024 (56) 9.4 / 10.9, 1114x512x512 (72) 7.9 / 7.5,
+//    300x2048x512 (80) 8.2 / 7.6.
+//  * 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
+//    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
+//    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
+//    stays until it needs more rounds of the GPU than 128x128 (2160x3072x1024: 28.7 / 24.5).
+//  * 256x256 where its tiles fill their last round of CUs to 90%: 16384x4096x1024 127 against
+//    142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90 against 82.
+//  * FP8 weights run on 128x128 only (their line: 1300x512x2048 (44 tiles of 128) 14.7 / 20.6,
+//    1114x1024x1024 (72) 15.3 / 12.9).
+static int phased_tile(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
+  if (dt == DT::F32 || K % 128 != 0) return 0;
+  constexpr unsigned long long lim = 1ull << 32;
+  const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
+  if (m * lda * 2 >= lim || n * K * 2 >= lim) return 0;
+  if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
+  const auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
+  if (epi.wscale) return t128 >= 64 ? 128 : 0;
+  if (epi.lnf_colsum) {
+    if (t64 < 64) return 0;
+    return (t128 + 511) / 512 < (t64 + 767) / 768 ? 128 : 64;
+  }
+  if (t64 < 112) return 0;
+  if (t64 <= 256) return 64;
+  const long long rounds = (t256 + 255) / 256;
+  return role == 0 && t256 * 10 >= rounds * 256 * 9 ? 256 : 128;
+}
+
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                 hipStream_t s, int role, int tile) {
   if (epi.wscale && dt != DT::F16) return hipErrorInvalidValue;   // FP8 weights pair with fp16
   // operand rows move in 16-byte pieces, and the kernel reads A's base as a stand-in
   if (((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Bt)) & 15) != 0) return hipErrorInvalidValue;
+  if (M > 0 && N > 0 && tile == 0) {
+    const int bm = phased_tile(dt, lda, M, N, K, epi, role);
+    if (bm) return dt == DT::F16 ? gemm_phased_f16(A, lda, Bt, M, N, K, epi, s, role, bm)
+                                 : gemm_phased_bf16(A, lda, Bt, M, N, K, epi, s, role, bm);
+  }
+  if (epi.mode == EPI_TOPK) tile = 2;   // the selection records assume 128-column tiles
   switch (dt) {
     case DT::F32: return launch_role<float>(A, lda, Bt, M, N, K, epi, s, role, tile);
     case DT::F16: return launch_role<f16>(A, lda, Bt, M, N, K, epi, s, role, tile);

@@ -95,7 +95,7 @@ struct GemmEpi {
   // LN(x) W + b up to rounding.
   const float* lnf_colsum = nullptr;
   float lnf_eps = 0.f;
-  // EPI_TOPK (the launch uses 128x128 tiles, so n_tiles = ceil(N / 128))
+  // EPI_TOPK (a record covers 128 columns, so n_tiles = ceil(N / 128))
   float* part = nullptr;           // [M][n_tiles][topk_record(k2)]
   int k2 = 1;                      // record layout: 1 (max, sum, best value, best column)
   int n_tiles = 0;
@@ -110,10 +110,17 @@ struct GemmEpi {
 
 // role: 0 encoder, 1 decoder step, 2 output projection.  Only the kernel's symbol name
 // depends on it, so profiles separate the three uses.  (Role 3 is gemm_pairs below.)
-// tile: 0 = chosen by shape, 1 = 64x32, 2 = 128x128, 3 = 128x64, 4 = 64x128 (never changes
-// a result).
+// tile: 0 = chosen by shape (among the phased tiles too), 1 = 64x32, 2 = 128x128, 3 = 128x64,
+// 4 = 64x128 (never changes a result).
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                 hipStream_t s, int role = 0, int tile = 0);
+
+// The same product on the phased tiles (nt_gemm_phased.h), bm x bm output tiles, bm = 128 or
+// 256; gemm() picks them by shape.
+hipError_t gemm_phased_f16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
+                           hipStream_t s, int role, int bm);
+hipError_t gemm_phased_bf16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
+                            hipStream_t s, int role, int bm);
 
 // The output projection's logits of chosen (row, 128-column tile) pairs, recomputed: for
 // every block of epi.gblk, the rows of its pairs times the tile's columns of Bt (N = V

@@ -785,11 +785,10 @@ nt_status enqueue_step(nt_dec_state* st, const int32_t* d_forced, float* d_logit
         if (e.mode == nt::EPI_TOPK) bytes += (double)R * e.n_tiles * nt::topk_record(e.k2) * 4.0;
       }
       const int role = cls == NT_K_GEMM_VOCAB ? 2 : 1;
-      const int tile = e.mode == nt::EPI_TOPK ? 2 : 0;   // the partial records assume 128-column tiles
       nt::GemmEpi ec = e;
       ec.ctl = ctl;
       ec.ctl_rows = K;
-      return timed(cls, s, bytes, 2.0 * R * N * Kd, [&] { return nt::gemm(m.dt, A, lda, W, Rp, N, Kd, ec, s, role, tile); });
+      return timed(cls, s, bytes, 2.0 * R * N * Kd, [&] { return nt::gemm(m.dt, A, lda, W, Rp, N, Kd, ec, s, role); });
     };
 
     // the first layer's ln1 output only when its QKV projection does not normalise itself

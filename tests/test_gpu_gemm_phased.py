@@ -1,0 +1,110 @@
+"""GPU: the phased GEMM tiles, which gemm() picks by shape, against the 64x32 tile.
+
+Both sum an element's products over K through the same MFMAs in the same order, so the
+results are equal bit for bit; the 64x32 tile itself is held to an fp64 product in
+test_gpu_gemm.py and test_gpu_gemm_ln.py.  The shapes sit on either side of each tile's
+edges: the first and last rows and columns of a tile, one k-step pair, ragged N with rows
+that vector stores cannot take, an output that starts unaligned.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+EPS = 1e-5
+
+
+def _bits(t):
+    import torch
+    return t.view(torch.int32 if t.element_size() == 4 else torch.int16)
+
+
+def _inputs(dtype, M, N, K, seed):
+    import torch
+    from paper_2109_08008_amd import nt
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    a = (r(M, K) + 0.3 * r(M, 1)).to(tdt)
+    w, scale = 0.1 * r(N, K), None
+    if dtype == "f8":
+        q, sc = nt.nt_quantize_fp8(w.T.cpu().numpy())
+        w, scale = torch.from_numpy(q).cuda(), torch.from_numpy(sc).cuda()
+    else:
+        w = w.to(tdt)
+    return a, w, scale, r(N), r(M, N).to(tdt)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+@pytest.mark.parametrize("M,N,K", [
+    (450, 2048, 128),      # 64x128 tiles, the last one of two rows, the shortest k-loop
+    (897, 1024, 384),      # 64x128: one row in the last tile
+    (4095, 1000, 512),     # 128x128, N ending inside a tile
+    (4225, 1031, 256),     # 128x128, rows of 1031 elements: no vector access
+    (4097, 4096, 256),     # 128x128 where 256x256 would leave a round nearly empty
+    (4096, 4096, 128),     # 256x256, whole tiles
+    (4081, 4092, 640),     # 256x256, ragged in both directions
+])
+def test_projection_equals_small_tile(dtype, M, N, K):
+    import torch
+    from paper_2109_08008_amd import nt
+    a, w, scale, bias, resid = _inputs(dtype, M, N, K, M + N + K)
+    for mode in ("store", "relu", "resid", "f32", "unaligned"):
+        got = []
+        for tile in (0, 1):
+            out = torch.full((M * N + 1,), float("nan"), device="cuda",
+                             dtype=torch.float32 if mode == "f32" else a.dtype)
+            at = out[1:] if mode == "unaligned" else out[:-1]
+            nt.nt_op_gemm("f16" if dtype == "f8" else dtype, a.data_ptr(), K, w.data_ptr(), M, N, K, bias.data_ptr(),
+                          resid.data_ptr() if mode == "resid" else None, at.data_ptr(), N, out_f32=mode == "f32",
+                          relu=mode == "relu", tile=tile, d_bscale=scale.data_ptr() if scale is not None else None)
+            torch.cuda.synchronize()
+            edge = out[0] if mode == "unaligned" else out[-1]
+            assert torch.isnan(edge), "stored past the output"
+            got.append(at)
+        assert torch.equal(_bits(got[0]), _bits(got[1])), mode
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+@pytest.mark.parametrize("M,N,K", [(513, 1024, 128), (1025, 1030, 384), (2111, 3072, 256), (449, 2048, 512)])
+def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
+    import torch
+    from paper_2109_08008_amd import nt
+    a, w, scale, bias, _ = _inputs(dtype, M, N, K, M + N + K)
+    wf = w.view(torch.float8_e4m3fn).double() * scale.double()[:, None] if dtype == "f8" else w.double()
+    colsum = wf.sum(1).float()
+    for relu in (False, True):
+        got = []
+        for tile in (0, 1):
+            out = torch.full((M, N), float("nan"), dtype=a.dtype, device="cuda")
+            nt.nt_op_gemm_ln("f16" if dtype == "f8" else dtype, a.data_ptr(), K, w.data_ptr(), M, N, K,
+                             colsum.data_ptr(), EPS, bias.data_ptr(), out.data_ptr(), N, relu=relu, tile=tile,
+                             d_bscale=scale.data_ptr() if scale is not None else None)
+            torch.cuda.synchronize()
+            got.append(out)
+        assert torch.equal(_bits(got[0]), _bits(got[1])), relu
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+def test_batch_size_does_not_change_a_translation(dtype):
+    """640 rows a step (phased tiles: cross keys/values, QKV with the cache scatter, FFN,
+    the selection records) against batches of eight sentences (the small tiles)."""
+    from paper_2109_08008_amd import nt
+    shape = synth.ModelShape(512, 8, 2048, 2, 2, 1100)
+    blob = synth.make_weights(shape, seed=5, lively=True)
+    rng = np.random.default_rng(6)
+    lens = rng.integers(20, 31, size=160)
+    offs = np.concatenate(([0], np.cumsum(lens))).astype(np.int64)
+    ids = rng.integers(4, shape.vocab, size=int(offs[-1])).astype(np.int32)
+    model = nt.Model(shape, blob, dtype)
+    base = synth.SearchSetup(beam=4, max_len_a=0.0, max_len_b=8, token_budget=0)
+    ref = model.translate(ids, offs, base)
+    got = model.translate(ids, offs, synth.replace(base, max_batch_sents=8))
+    for a, b in zip(ref[0], got[0]):
+        np.testing.assert_array_equal(a, b)
+    np.testing.assert_array_equal(ref[1], got[1])
+    for a, b in zip(ref[2], got[2]):
+        np.testing.assert_array_equal(a, b)
+    model.close()
