@@ -714,40 +714,36 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
   return hipErrorInvalidValue;
 }
 
-// Rows (and, but for 64, columns) of the phased tile a product runs on, or 0 for the tiles of
-// this file.  Both give the same bits.  Measured on MI355X, launches of one shape replayed
-// back to back from a graph (us, this file's tile against the phased one):
-//  * K in whole pairs of 64 (an even number of k-steps), 16-bit activations, and operands
-//    within 32-bit byte offsets are what the phased kernel takes.
-//  * The output projection always (16x32000x512 12.6 / 8.5, 1300x32000x512 78 / 52).
-//  * Else by the number of 64x128 tiles (T64), a CU's worth of work each.  Few tiles leave most
-//    CUs idle, and the 64x32 tiles below, four times as many, finish first: 1500x512x512 (96
-//    tiles) 5.5 / 6.3, 800x1024x4096 (104) 20.8 / 24.1; from 112 on the phased tile wins:
-//    1114x1024x4096 (144) 38.3 / 24.5, 700x1536x512 (132) 7.7 / 6.2.  With a folded LayerNorm
-//    the line lies at 64 tiles: 400x1024x1024 (56) 9.4 / 10.9, 1114x512x512 (72) 7.9 / 7.5,
-//    300x2048x512 (80) 8.2 / 7.6.
-//  * 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
+// Rows of the phased tile a product runs on (nt_gemm_phased.h), or 0 for the tiles of this file.
+// All give the same bits.  Measured on MI355X, launches of one shape replayed back to back
+// from a graph (us):
+//  * 16-bit activations and operands within 32-bit byte offsets are what the phased kernels
+//    take, and all but the 64x32 one an even number of k-steps.
+//  * The output projection always runs on 128x128 (this file's tile / phased: 16x32000x512 12.6 /
+//    8.5, 1300x32000x512 78 / 52).
+//  * Up to 512 tiles of 64x32, two a CU, those (32): 552x3072x1024 with a folded LayerNorm, 864
+//    tiles, takes 16.1 against 11.5 on 64x128, 300x3072x1024 (480) 9.2 against 11.0,
+//    800x1024x4096 (416) 20.5 against 23.2, 1114x1024x1024 (576) 10.5 against 8.8.
+//  * Then 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
 //    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
 //    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
 //    stays until it needs more rounds of the GPU than 128x128 (2160x3072x1024: 28.7 / 24.5).
 //  * 256x256 where its tiles fill their last round of CUs to 90%: 16384x4096x1024 127 against
 //    142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90 against 82.
-//  * FP8 weights run on 128x128 only (their line: 1300x512x2048 (44 tiles of 128) 14.7 / 20.6,
-//    1114x1024x1024 (72) 15.3 / 12.9).
+//  * FP8 weights run on 128x128 from 64 tiles on (this file's / phased: 1300x512x2048, 44 tiles,
+//    14.7 / 20.6; 1114x1024x1024, 72, 15.3 / 12.9).
 static int phased_tile(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
-  if (dt == DT::F32 || K % 128 != 0) return 0;
+  if (dt == DT::F32) return 0;
   constexpr unsigned long long lim = 1ull << 32;
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
   if (m * lda * 2 >= lim || n * K * 2 >= lim) return 0;
-  if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
   const auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (role != 2 && !epi.wscale && tiles(64, 32) <= 512) return 32;
+  if (K % 128 != 0) return 0;
+  if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
   const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
   if (epi.wscale) return t128 >= 64 ? 128 : 0;
-  if (epi.lnf_colsum) {
-    if (t64 < 64) return 0;
-    return (t128 + 511) / 512 < (t64 + 767) / 768 ? 128 : 64;
-  }
-  if (t64 < 112) return 0;
+  if (epi.lnf_colsum) return (t128 + 511) / 512 < (t64 + 767) / 768 ? 128 : 64;
   if (t64 <= 256) return 64;
   const long long rounds = (t256 + 255) / 256;
   return role == 0 && t256 * 10 >= rounds * 256 * 9 ? 256 : 128;

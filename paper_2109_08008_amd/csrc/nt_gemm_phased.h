@@ -221,6 +221,7 @@ NT_PHASE_STRUCT(bf16)
 __device__ __forceinline__ void dma16(const char* src, unsigned char* dst) {
   __builtin_amdgcn_global_load_lds(src, NT_LDS(dst), 16, 0, 0);
 }
+__device__ __forceinline__ unsigned uniform(unsigned v) { return __builtin_amdgcn_readfirstlane(v); }
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory"); }
 // The MFMAs of an asm block may still be writing their results when it ends.
@@ -343,17 +344,40 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
   if (LNF) al |= reinterpret_cast<uintptr_t>(epi.lnf_colsum);
 
   if (nw + FN * 16 > N || (al & 15) != 0) {
+    if constexpr (FM == 1) {   // a ragged or unaligned tile, four columns at a time
+      auto finish = [&](auto mode_c) {
+        constexpr int MODE = decltype(mode_c)::value;
+        const int m = mw + fr;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int n = nw + j * 16 + 4 * fc;
+          if (m >= M || n >= N) continue;
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int cc = min(n + r, N - 1);
+            v[r] = c[0][j][r];
+            if constexpr (F8) v[r] *= epi.wscale[cc];
+            if constexpr (LNF) v[r] = (v[r] - mu[0] * epi.lnf_colsum[cc]) * rs[0];
+            if constexpr (F8 || LNF) asm("" : "+v"(v[r]));   // rounded before the bias is added, as where staged
+          }
+          epilogue4<T, MODE, true>(epi, m, n, N, make_float4(v[0], v[1], v[2], v[3]), t_slot);
+        }
+      };
+      mode_switch<ROLE>(epi.mode, finish);
+      return;
+    }
     // a ragged or unaligned tile: its halves through LDS (the wave's own part), then four
     // columns at a time
-    constexpr int HROWS = FM * 8, CS = FN * 16 + 4;
+    constexpr int HROWS = FM * 8, CS = FN * 16 + 4, FH = FM > 1 ? FM / 2 : 1;
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
-        if (i / (FM / 2) == h) {
+        if (i / FH == h) {
 #pragma unroll
           for (int j = 0; j < FN; ++j)
-            *reinterpret_cast<floatx4*>(&cs[(i % (FM / 2) * 16 + fr) * CS + j * 16 + 4 * fc]) = c[i][j];
+            *reinterpret_cast<floatx4*>(&cs[(i % FH * 16 + fr) * CS + j * 16 + 4 * fc]) = c[i][j];
         }
       wave_lds_fence();
       auto finish = [&](auto mode_c) {
@@ -782,6 +806,176 @@ __global__ __launch_bounds__(W::WGM * W::WGN * kWave, 2) void gemm_phased_kernel
                                             ln_mu + wm * (FM * 16), ln_rs + wm * (FM * 16));
 }
 
+// ---- few tiles: 64x32, one phase a k-step ----------------------------------------------------
+// Where a product has few tiles for the GPU's CUs, a tile's own chain bounds the launch: four
+// phases a k-step cost four LDS round trips and barriers.  Here a k-step is one phase: a wave
+// (16 rows, two blocks of columns) multiplies while it reads the next k-step's fragments, and
+// NS k-steps in LDS give the direct loads NS - 2 phases to land.  A k-step takes 0.13 us
+// against 0.28 on the three- and four-stage 64x32 tiles of nt_gemm.hip and 0.4 on the 64x128
+// phased tile with one workgroup a CU.  Measured (us, nt_gemm.hip's tile / this): a step's
+// projections at 128 rows, 1536x512 with a folded LayerNorm 6.4 / 5.1, 512x512 4.6 / 4.1,
+// 512x2048 9.9 / 7.4, 1024x4096 17.1 / 11.9.  Six k-steps (72 KB, two workgroups a CU): eight and
+// ten are no faster alone and slower from 256 tiles on (300x3072x1024 9.2, 12.5, 12.9), where
+// the second workgroup has to wait.
+#define NT_S2(RB0, RB1, RB2, RB3, LD)                                                               \
+  "ds_read_b128 %[na0], %[pa0]\n\tds_read_b128 %[na1], %[pa1]\n\t"                                 \
+  NT_MM("c0", "b00", "a0") RB0 RB1 NT_MM("c1", "b10", "a0") RB2 RB3                                 \
+  LD NT_MM("c0", "b01", "a1") NT_MM("c1", "b11", "a1")
+#define NT_S_LD3                                                                                    \
+  "s_mov_b32 m0, %[ma]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xa0], %[sa]\n\t"                    \
+  "s_add_u32 m0, %[ma], 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xa1], %[sa]\n\t"             \
+  "s_mov_b32 m0, %[mb]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xb], %[sb]\n\t"
+template <typename T> struct SlimPhase;
+#define NT_SLIM_STRUCT(TYPE)                                                                        \
+  template <> struct SlimPhase<TYPE> {                                                              \
+    template <int OB, int VM>                                                                       \
+    static __device__ __forceinline__ void step(floatx4 (&c)[1][2], const u32x4 (&a)[2],            \
+                                                const u32x4 (&b)[2][2], u32x4 (&na)[2],             \
+                                                u32x4 (&nb)[2][2], unsigned pa0, unsigned pa1,      \
+                                                unsigned pb0, unsigned pb1, const unsigned* xa,     \
+                                                const char* sa, unsigned ma, unsigned xb,           \
+                                                const char* sb, unsigned mb) {                      \
+      asm volatile(NT_S2("ds_read_b128 %[nb00], %[pb0] offset:%[o0]\n\t",                           \
+                         "ds_read_b128 %[nb01], %[pb1] offset:%[o0]\n\t",                           \
+                         "ds_read_b128 %[nb10], %[pb0] offset:%[o1]\n\t",                           \
+                         "ds_read_b128 %[nb11], %[pb1] offset:%[o1]\n\t", NT_S_LD3) NT_END          \
+                   : [c0] "+v"(c[0][0]), [c1] "+v"(c[0][1]), [na0] "=&v"(na[0]), [na1] "=&v"(na[1]), \
+                     [nb00] "=&v"(nb[0][0]), [nb01] "=&v"(nb[0][1]), [nb10] "=&v"(nb[1][0]),        \
+                     [nb11] "=&v"(nb[1][1])                                                         \
+                   : [a0] "v"(a[0]), [a1] "v"(a[1]), [b00] "v"(b[0][0]), [b01] "v"(b[0][1]),        \
+                     [b10] "v"(b[1][0]), [b11] "v"(b[1][1]), [pa0] "v"(pa0), [pa1] "v"(pa1),        \
+                     [pb0] "v"(pb0), [pb1] "v"(pb1), [o0] "i"(OB), [o1] "i"(OB + 16 * ROWB),        \
+                     [xa0] "v"(xa[0]), [xa1] "v"(xa[1]), [sa] "s"(sa), [ma] "s"(ma), [xb] "v"(xb),  \
+                     [sb] "s"(sb), [mb] "s"(mb), [vm] "i"(VM)                                       \
+                   : "memory", "m0", "scc");                                                        \
+    }                                                                                               \
+  };
+#define NT_MFMA_T "f16"
+NT_SLIM_STRUCT(f16)
+#undef NT_MFMA_T
+#define NT_MFMA_T "bf16"
+NT_SLIM_STRUCT(bf16)
+#undef NT_MFMA_T
+
+template <typename T, int NS, int ROLE, bool LNF>
+__global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A, int lda, const void* __restrict__ Bt,
+                                                        int M, int N, int K, GemmEpi epi, int tiles_m, int tiles_n) {
+  constexpr int BM = 64, BN = 32, FN = 2;
+  constexpr int AB = BM * ROWB, BB = BN * ROWB, SLOT = AB + BB;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * SLOT];
+
+  asm volatile("" ::"s"(epi.ctl), "s"(epi.bias), "s"(epi.out), "s"(epi.ldc), "s"(epi.wscale), "s"(epi.part),
+               "s"(tiles_n), "s"(M), "s"(Bt));
+  if (epi.ctl) {
+    M = min(M, epi.ctl[CTL_NLIVE] * epi.ctl_rows);
+    tiles_m = (M + BM - 1) / BM;
+  }
+  const int ntiles = tiles_m * tiles_n;
+  int pid = blockIdx.x;
+  if (pid >= ntiles) return;
+  {
+    const int q = ntiles / 8, r = ntiles % 8, xcd = pid % 8, idx = pid / 8;
+    pid = xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+  }
+  constexpr int GROUP = 8;
+  const int per_group = GROUP * tiles_n;
+  const int first_m = (pid / per_group) * GROUP;
+  const int gsize = min(tiles_m - first_m, GROUP);
+  const int tm = first_m + (pid % per_group) % gsize, tn = (pid % per_group) / gsize;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int t_slot = epi.ctl ? epi.ctl[CTL_T] : epi.t;
+
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int fr = lane & 15, fc = lane >> 4;
+
+  // direct loads: 8 rows of 128 bytes each; two of A and one of B a wave and k-step
+  const unsigned lda_b = (unsigned)lda * sizeof(T), ldb_b = (unsigned)K * sizeof(T);
+  const unsigned ch = ((lane & 7) ^ (lane >> 3)) << 4;
+  unsigned xa[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) xa[i] = (unsigned)min(m0 + (wave * 2 + i) * 8 + (lane >> 3), M - 1) * lda_b + ch;
+  const unsigned xb = (unsigned)min(n0 + wave * 8 + (lane >> 3), N - 1) * ldb_b + ch;
+  const char* Ab = reinterpret_cast<const char*>(A);
+  const char* Bb = static_cast<const char*>(Bt);
+  const unsigned lb = (unsigned)(uintptr_t)NT_LDS(lds);
+  const unsigned ma = lb + wave * 2048, mb = lb + AB + wave * 1024;
+  // lane addresses of the fragments in slot 0; the halves of a k-step differ in one bit
+  const unsigned pa = lb + (wave * 16 + fr) * ROWB + ((fc ^ (fr & 7)) << 4);
+  const unsigned pb = lb + AB + fr * ROWB + ((fc ^ (fr & 7)) << 4);
+
+  const int nk = (int)((size_t)K * sizeof(T) / ROWB);
+#pragma unroll
+  for (int kt = 0; kt < NS; ++kt) {   // past the last k-step: its bytes again, never read
+    const size_t at = (size_t)min(kt, nk - 1) * ROWB;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) dma16(Ab + at + xa[i], lds + kt * SLOT + wave * 2048 + i * 1024);
+    dma16(Bb + at + xb, lds + kt * SLOT + AB + wave * 1024);
+  }
+  floatx4 acc[1][FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) acc[0][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  constexpr int VM = (NS - 2) * 3;   // the loads behind the k-step after the next
+  wait_vm<VM>();
+  __builtin_amdgcn_s_barrier();
+  u32x4 a0[2], a1[2], b0[FN][2], b1[FN][2];
+  {
+    u32x4 t[1][2];
+    lds_frags<0>(t, pa, pa ^ 64);
+    a0[0] = t[0][0];
+    a0[1] = t[0][1];
+    lds_frags<0>(b0, pb, pb ^ 64);
+  }
+  __builtin_amdgcn_s_barrier();
+  float ls = 0.f, lq = 0.f;
+  T sh{};
+  if constexpr (LNF) sh = __builtin_bit_cast(T, (unsigned short)(__shfl(a0[0].x, fr, kWave) & 0xffffu));
+
+  unsigned s0 = 0, s1 = SLOT;   // slots of this k-step and the next
+  auto kstep = [&](int kt, u32x4 (&a)[2], u32x4 (&b)[FN][2], u32x4 (&na)[2], u32x4 (&nb)[FN][2]) {
+    const size_t at = (size_t)min(kt + NS, nk - 1) * ROWB;
+    const unsigned qa = pa + s1, qb = pb + s1;
+    SlimPhase<T>::template step<0, VM>(acc, a, b, na, nb, qa, qa ^ 64, qb, qb ^ 64, xa, Ab + at, uniform(ma + s0), xb,
+                                       Bb + at, uniform(mb + s0));
+    if constexpr (LNF) {
+      frag_stats<T>(a[0], sh, ls, lq);
+      frag_stats<T>(a[1], sh, ls, lq);
+    }
+    s0 = s1;
+    s1 = s1 == (NS - 1) * SLOT ? 0 : s1 + SLOT;
+  };
+  for (int kt = 0;;) {
+    kstep(kt, a0, b0, a1, b1);
+    if (++kt >= nk) break;
+    kstep(kt, a1, b1, a0, b0);
+    if (++kt >= nk) break;
+  }
+  mfma_drain();
+  float mu[1] = {0.f}, rs[1] = {1.f};
+  if constexpr (LNF) {   // every lane of a row ends with its sums
+    const float inv_k = 1.0f / (float)K;
+    ls += __shfl_xor(ls, 16, kWave);
+    lq += __shfl_xor(lq, 16, kWave);
+    ls += __shfl_xor(ls, 32, kWave);
+    lq += __shfl_xor(lq, 32, kWave);
+    const float ms = ls * inv_k;
+    const float var = fmaxf(lq * inv_k - ms * ms, 0.f);
+    mu[0] = to_f32(sh) + ms;
+    rs[0] = 1.0f / sqrtf(var + epi.lnf_eps);
+  }
+  phased_epilogue<T, 1, FN, ROLE, false, LNF>(acc, epi, M, N, m0 + wave * 16, n0, t_slot, fr, fc, mu, rs, nullptr,
+                                              nullptr, nullptr);
+  wait_vm<0>();   // no load into LDS outlives the workgroup
+}
+
+template <typename T, int NS, int ROLE, bool LNF>
+hipError_t launch_slim(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi, hipStream_t s) {
+  const int tm = (M + 63) / 64, tn = (N + 31) / 32;
+  NT_LAUNCH((gemm_slim_kernel<T, NS, ROLE, LNF>), dim3(tm * tn), dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
+            K, epi, tm, tn);
+  return hipGetLastError();
+}
+
 template <typename T, typename W, int ROLE, bool F8, bool LNF>
 hipError_t launch_phased(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                          hipStream_t s) {
@@ -800,6 +994,7 @@ hipError_t launch_tile(const void* A, int lda, const void* Bt, int M, int N, int
   } else {
     if constexpr (std::is_same<T, f16>::value)
       if (epi.wscale) return launch_phased<T, Tile128, ROLE, true, LNF>(A, lda, Bt, M, N, K, epi, s);
+    if (bm == 32) return launch_slim<T, 6, ROLE, LNF>(A, lda, Bt, M, N, K, epi, s);
     if (bm == 64) return launch_phased<T, Tile64, ROLE, false, LNF>(A, lda, Bt, M, N, K, epi, s);
     if constexpr (ROLE == 0)
       if (bm == 256) return launch_phased<T, Tile256, ROLE, false, false>(A, lda, Bt, M, N, K, epi, s);

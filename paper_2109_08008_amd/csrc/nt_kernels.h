@@ -115,8 +115,8 @@ struct GemmEpi {
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                 hipStream_t s, int role = 0, int tile = 0);
 
-// The same product on the phased tiles (nt_gemm_phased.h), bm x bm output tiles, bm = 128 or
-// 256; gemm() picks them by shape.
+// The same product on the phased tiles (nt_gemm_phased.h), bm = 32: 64x32 output
+// tiles; 64: 64x128; 128 and 256: bm x bm.  gemm() picks them by shape.
 hipError_t gemm_phased_f16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                            hipStream_t s, int role, int bm);
 hipError_t gemm_phased_bf16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,

@@ -39,6 +39,9 @@ def _inputs(dtype, M, N, K, seed):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
 @pytest.mark.parametrize("M,N,K", [
+    (1, 8, 64),            # 64x32 tiles: one row, one k-step
+    (65, 100, 192),        # 64x32: two rows of tiles, an odd number of k-steps, ragged N
+    (128, 2050, 2048),     # 64x32: more k-steps than LDS holds, two columns in the last tile
     (450, 2048, 128),      # 64x128 tiles, the last one of two rows, the shortest k-loop
     (897, 1024, 384),      # 64x128: one row in the last tile
     (4095, 1000, 512),     # 128x128, N ending inside a tile
@@ -68,7 +71,7 @@ def test_projection_equals_small_tile(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
-@pytest.mark.parametrize("M,N,K", [(513, 1024, 128), (1025, 1030, 384), (2111, 3072, 256), (449, 2048, 512)])
+@pytest.mark.parametrize("M,N,K", [(3, 40, 64), (65, 1000, 448), (513, 1024, 128), (1025, 1030, 384), (2111, 3072, 256), (449, 2048, 512)])
 def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
     import torch
     from paper_2109_08008_amd import nt
