@@ -17,7 +17,8 @@ ROOT = os.path.dirname(HERE)
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(HERE, "libnt.so")
 
-SOURCES = ["nt_gemm.hip", "nt_gemm_phased_f16.hip", "nt_gemm_phased_bf16.hip", "nt_norm.hip", "nt_attn.hip", "nt_search.hip", "nt_runtime.cpp"]
+SOURCES = ["nt_gemm.hip", "nt_gemm_phased_f16.hip", "nt_gemm_phased_bf16.hip", "nt_gemm_phased_f32.hip",
+           "nt_norm.hip", "nt_attn.hip", "nt_search.hip", "nt_runtime.cpp"]
 ARCH = "gfx950"
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",

@@ -732,13 +732,17 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90 against 82.
 //  * FP8 weights run on 128x128 from 64 tiles on (this file's / phased: 1300x512x2048, 44 tiles,
 //    14.7 / 20.6; 1114x1024x1024, 72, 15.3 / 12.9).
+//  * fp32 runs on 64x32 up to 512 of them (1000x512x512 9.4 / 8.2, 8x384x128 with a folded
+//    LayerNorm 5.2 / 4.5), and encoder products beyond on 64x64 (4096x512x512 26.5 / 24.1,
+//    16384x1024x256 93.8 / 80.1): an fp32 k-step is bound by its MFMAs, so what counts is that
+//    the reads and loads stay behind them.
 static int phased_tile(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
-  if (dt == DT::F32) return 0;
   constexpr unsigned long long lim = 1ull << 32;
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
-  if (m * lda * 2 >= lim || n * K * 2 >= lim) return 0;
+  if (m * lda * dt_bytes(dt) >= lim || n * K * dt_bytes(dt) >= lim) return 0;
   const auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (role != 2 && !epi.wscale && tiles(64, 32) <= 512) return 32;
+  if (dt == DT::F32) return role == 0 ? 64 : 0;
   if (K % 128 != 0) return 0;
   if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
   const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
@@ -756,10 +760,14 @@ hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int
   if (((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Bt)) & 15) != 0) return hipErrorInvalidValue;
   if (M > 0 && N > 0 && tile == 0) {
     const int bm = phased_tile(dt, lda, M, N, K, epi, role);
-    if (bm) return dt == DT::F16 ? gemm_phased_f16(A, lda, Bt, M, N, K, epi, s, role, bm)
-                                 : gemm_phased_bf16(A, lda, Bt, M, N, K, epi, s, role, bm);
+    if (bm) return dt == DT::F16    ? gemm_phased_f16(A, lda, Bt, M, N, K, epi, s, role, bm)
+                   : dt == DT::BF16 ? gemm_phased_bf16(A, lda, Bt, M, N, K, epi, s, role, bm)
+                                    : gemm_slim_f32(A, lda, Bt, M, N, K, epi, s, role, bm);
   }
-  if (epi.mode == EPI_TOPK) tile = 2;   // the selection records assume 128-column tiles
+  // The selection records assume 128-column tiles.  A step of at most 64 rows leaves half of a
+  // 128-row tile empty (fp32, 8 rows: 1000x128 15.3 us against 8.8 on 64x128, 32000x512 42.9
+  // against 23.7).
+  if (epi.mode == EPI_TOPK) tile = M <= 64 ? 4 : 2;
   switch (dt) {
     case DT::F32: return launch_role<float>(A, lda, Bt, M, N, K, epi, s, role, tile);
     case DT::F16: return launch_role<f16>(A, lda, Bt, M, N, K, epi, s, role, tile);

@@ -227,6 +227,12 @@ __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :
 // The MFMAs of an asm block may still be writing their results when it ends.
 __device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
+// The first element of a word.
+template <typename T>
+__device__ __forceinline__ T first_value(unsigned w) {
+  if constexpr (sizeof(T) == 2) return __builtin_bit_cast(T, (unsigned short)(w & 0xffffu));
+  else return __builtin_bit_cast(T, w);
+}
 // Orders a wave's LDS writes before its own reads of what other lanes wrote.
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
@@ -434,7 +440,7 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
 #pragma unroll
     for (int j = 0; j < FN; ++j)
       b4[j] = epi.bias ? *reinterpret_cast<const float4*>(epi.bias + nw + j * 16 + 4 * fc) : make_float4(0.f, 0.f, 0.f, 0.f);
-    constexpr bool RES = MODE == EPI_RESID;
+    constexpr bool RES = MODE == EPI_RESID && sizeof(T) == 2;
     uint4 res[RES ? FM : 1][RES ? FN / 2 : 1];
     if constexpr (RES) {   // every residual before the first store (the output may alias it)
 #pragma unroll
@@ -462,6 +468,27 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
         cell = ((size_t)b * epi.H * epi.S + (m - b * epi.S)) * epi.dh;
       }
       if (m >= M) continue;
+      auto cache_of = [&](auto elem, int n) {   // column n >= d of the row, in the step's cache slot
+        int cd = n - epi.d;
+        const int kv = cd >= epi.d;
+        cd -= kv * epi.d;
+        const int hd = cd / epi.dh, x = cd - hd * epi.dh;
+        return static_cast<decltype(elem)*>(kv ? epi.vcache : epi.kcache) + cell + (size_t)hd * epi.Tcap * epi.dh + x;
+      };
+      auto cell_of = [&](int n) -> T* {         // column n of the row
+        if constexpr (MODE == EPI_SELF_QKV) {
+          if (n >= epi.d) return cache_of(T{}, n);
+        }
+        if constexpr (MODE == EPI_CROSS_KV) {
+          const int jl = n / (2 * epi.d);
+          int cd = n - jl * 2 * epi.d;
+          const int kv = cd >= epi.d;
+          cd -= kv * epi.d;
+          const int hd = cd / epi.dh, x = cd - hd * epi.dh;
+          return static_cast<T*>(epi.cross) + (((size_t)jl * 2 + kv) * epi.B * epi.H + hd) * (size_t)epi.S * epi.dh + x + cell;
+        }
+        return static_cast<T*>(epi.out) + row + n;
+      };
 #pragma unroll
       for (int jp = 0; jp < FN / 2; ++jp) {
         float v[2][4];
@@ -487,58 +514,50 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
             continue;
           }
         }
-        if constexpr (RES) {   // the residual's words back into the blocks' layout
-          uint4 q = res[i][jp];
+        if constexpr (sizeof(T) == 4) {   // four columns a lane are 16 bytes already
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int nu = n + u * 16 + 4 * fc;
+            if constexpr (MODE == EPI_RESID) {
+              const floatx4 q = *reinterpret_cast<const floatx4*>(static_cast<const float*>(epi.resid) + row + nu);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) v[u][r] += q[r];
+            }
+            *reinterpret_cast<float4*>(cell_of(n) + u * 16 + 4 * fc) = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+          }
+        } else {
+          if constexpr (RES) {   // the residual's words back into the blocks' layout
+            uint4 q = res[i][jp];
+            row_swap(q.x, q.z);
+            row_swap(q.y, q.w);
+            const unsigned w[4] = {q.x, q.y, q.z, q.w};
+  #pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float2 f = unpack2<T>(w[r]);
+              v[r / 2][r % 2 * 2] += f.x;
+              v[r / 2][r % 2 * 2 + 1] += f.y;
+            }
+          }
+          if constexpr (MODE == EPI_SELF_QKV && std::is_same<T, f16>::value) {
+            if (epi.kv_f8 && n >= epi.d) {   // E4M3 cache
+              uint8_t* o8 = cache_of(uint8_t{}, n);
+  #pragma unroll
+              for (int u = 0; u < 2; ++u)
+                *reinterpret_cast<uint32_t*>(o8 + u * 16 + 4 * fc) =
+                    (uint32_t)e4m3_rne(v[u][0]) | ((uint32_t)e4m3_rne(v[u][1]) << 8) |
+                    ((uint32_t)e4m3_rne(v[u][2]) << 16) | ((uint32_t)e4m3_rne(v[u][3]) << 24);
+              continue;
+            }
+          }
+          uint4 q;
+          q.x = pack2<T>(v[0][0], v[0][1]);
+          q.y = pack2<T>(v[0][2], v[0][3]);
+          q.z = pack2<T>(v[1][0], v[1][1]);
+          q.w = pack2<T>(v[1][2], v[1][3]);
           row_swap(q.x, q.z);
           row_swap(q.y, q.w);
-          const unsigned w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float2 f = unpack2<T>(w[r]);
-            v[r / 2][r % 2 * 2] += f.x;
-            v[r / 2][r % 2 * 2 + 1] += f.y;
-          }
+          *reinterpret_cast<uint4*>(cell_of(n) + n8) = q;
         }
-        T* o;
-        if constexpr (MODE == EPI_SELF_QKV) {
-          if (n >= epi.d) {
-            int cd = n - epi.d;
-            const int kv = cd >= epi.d;
-            cd -= kv * epi.d;
-            const int hd = cd / epi.dh, x = cd - hd * epi.dh;
-            const size_t col = (size_t)hd * epi.Tcap * epi.dh + x;
-            if constexpr (std::is_same<T, f16>::value) {
-              if (epi.kv_f8) {   // E4M3 cache
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                  *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(kv ? epi.vcache : epi.kcache) + cell + col + u * 16 + 4 * fc) =
-                      (uint32_t)e4m3_rne(v[u][0]) | ((uint32_t)e4m3_rne(v[u][1]) << 8) |
-                      ((uint32_t)e4m3_rne(v[u][2]) << 16) | ((uint32_t)e4m3_rne(v[u][3]) << 24);
-                continue;
-              }
-            }
-            o = static_cast<T*>(kv ? epi.vcache : epi.kcache) + cell + col;
-          } else {
-            o = static_cast<T*>(epi.out) + row + n;
-          }
-        } else if constexpr (MODE == EPI_CROSS_KV) {
-          const int jl = n / (2 * epi.d);
-          int cd = n - jl * 2 * epi.d;
-          const int kv = cd >= epi.d;
-          cd -= kv * epi.d;
-          const int hd = cd / epi.dh, x = cd - hd * epi.dh;
-          o = static_cast<T*>(epi.cross) + (((size_t)jl * 2 + kv) * epi.B * epi.H + hd) * (size_t)epi.S * epi.dh + x + cell;
-        } else {
-          o = static_cast<T*>(epi.out) + row + n;
-        }
-        uint4 q;
-        q.x = pack2<T>(v[0][0], v[0][1]);
-        q.y = pack2<T>(v[0][2], v[0][3]);
-        q.z = pack2<T>(v[1][0], v[1][1]);
-        q.w = pack2<T>(v[1][2], v[1][3]);
-        row_swap(q.x, q.z);
-        row_swap(q.y, q.w);
-        *reinterpret_cast<uint4*>(o + n8) = q;
       }
     }
   };
@@ -706,7 +725,7 @@ __global__ __launch_bounds__(W::WGM * W::WGN * kWave, 2) void gemm_phased_kernel
     for (int i = 0; i < FMH; ++i) {
       // chunk 0 of the row is in lane group 0 of the first half of the k-step
       const unsigned w = __shfl(wn ? ay[i][0].x : ax[i][0].x, fr, kWave);
-      lsh[i] = __builtin_bit_cast(T, (unsigned short)(w & 0xffffu));
+      lsh[i] = first_value<T>(w);
     }
   }
   __builtin_amdgcn_s_barrier();
@@ -825,15 +844,15 @@ __global__ __launch_bounds__(W::WGM * W::WGN * kWave, 2) void gemm_phased_kernel
   "s_mov_b32 m0, %[ma]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xa0], %[sa]\n\t"                    \
   "s_add_u32 m0, %[ma], 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xa1], %[sa]\n\t"             \
   "s_mov_b32 m0, %[mb]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[xb], %[sb]\n\t"
-template <typename T> struct SlimPhase;
+template <typename T, int FN> struct SlimPhase;
 #define NT_SLIM_STRUCT(TYPE)                                                                        \
-  template <> struct SlimPhase<TYPE> {                                                              \
+  template <> struct SlimPhase<TYPE, 2> {                                                             \
     template <int OB, int VM>                                                                       \
     static __device__ __forceinline__ void step(floatx4 (&c)[1][2], const u32x4 (&a)[2],            \
                                                 const u32x4 (&b)[2][2], u32x4 (&na)[2],             \
                                                 u32x4 (&nb)[2][2], unsigned pa0, unsigned pa1,      \
                                                 unsigned pb0, unsigned pb1, const unsigned* xa,     \
-                                                const char* sa, unsigned ma, unsigned xb,           \
+                                                const char* sa, unsigned ma, const unsigned* xb,    \
                                                 const char* sb, unsigned mb) {                      \
       asm volatile(NT_S2("ds_read_b128 %[nb00], %[pb0] offset:%[o0]\n\t",                           \
                          "ds_read_b128 %[nb01], %[pb1] offset:%[o0]\n\t",                           \
@@ -845,7 +864,7 @@ template <typename T> struct SlimPhase;
                    : [a0] "v"(a[0]), [a1] "v"(a[1]), [b00] "v"(b[0][0]), [b01] "v"(b[0][1]),        \
                      [b10] "v"(b[1][0]), [b11] "v"(b[1][1]), [pa0] "v"(pa0), [pa1] "v"(pa1),        \
                      [pb0] "v"(pb0), [pb1] "v"(pb1), [o0] "i"(OB), [o1] "i"(OB + 16 * ROWB),        \
-                     [xa0] "v"(xa[0]), [xa1] "v"(xa[1]), [sa] "s"(sa), [ma] "s"(ma), [xb] "v"(xb),  \
+                     [xa0] "v"(xa[0]), [xa1] "v"(xa[1]), [sa] "s"(sa), [ma] "s"(ma), [xb] "v"(xb[0]), \
                      [sb] "s"(sb), [mb] "s"(mb), [vm] "i"(VM)                                       \
                    : "memory", "m0", "scc");                                                        \
     }                                                                                               \
@@ -857,10 +876,74 @@ NT_SLIM_STRUCT(f16)
 NT_SLIM_STRUCT(bf16)
 #undef NT_MFMA_T
 
-template <typename T, int NS, int ROLE, bool LNF>
+// fp32: a 16-byte chunk is four MFMAs a block, its words named one by one; they go round the two
+// blocks, so that an MFMA does not wait for the one before it.
+#define NT_FM(c, b, a) "v_mfma_f32_16x16x4_f32 %[" c "], %[" b "], %[" a "], %[" c "]\n\t"
+#define NT_F2(h, w) NT_FM("c0", "p" h w, "a" h w) NT_FM("c1", "q" h w, "a" h w)
+#define NT_WORDS(n, v) [n##0] "v"(v.x), [n##1] "v"(v.y), [n##2] "v"(v.z), [n##3] "v"(v.w)
+template <> struct SlimPhase<float, 2> {
+  template <int OB, int VM>
+  static __device__ __forceinline__ void step(floatx4 (&c)[1][2], const u32x4 (&a)[2], const u32x4 (&b)[2][2],
+                                              u32x4 (&na)[2], u32x4 (&nb)[2][2], unsigned pa0, unsigned pa1,
+                                              unsigned pb0, unsigned pb1, const unsigned* xa, const char* sa,
+                                              unsigned ma, const unsigned* xb, const char* sb, unsigned mb) {
+    asm volatile("ds_read_b128 %[na0], %[r0]\n\tds_read_b128 %[na1], %[r1]\n\t"
+                 NT_F2("0", "0") "ds_read_b128 %[nb00], %[t0] offset:%[o0]\n\t"
+                 "ds_read_b128 %[nb01], %[t1] offset:%[o0]\n\t"
+                 NT_F2("0", "1") "ds_read_b128 %[nb10], %[t0] offset:%[o1]\n\t"
+                 "ds_read_b128 %[nb11], %[t1] offset:%[o1]\n\t"
+                 NT_F2("0", "2") NT_S_LD3 NT_F2("0", "3")
+                 NT_F2("1", "0") NT_F2("1", "1") NT_F2("1", "2") NT_F2("1", "3") NT_END
+                 : [c0] "+v"(c[0][0]), [c1] "+v"(c[0][1]), [na0] "=&v"(na[0]), [na1] "=&v"(na[1]),
+                   [nb00] "=&v"(nb[0][0]), [nb01] "=&v"(nb[0][1]), [nb10] "=&v"(nb[1][0]), [nb11] "=&v"(nb[1][1])
+                 : NT_WORDS(a0, a[0]), NT_WORDS(a1, a[1]), NT_WORDS(p0, b[0][0]), NT_WORDS(p1, b[0][1]),
+                   NT_WORDS(q0, b[1][0]), NT_WORDS(q1, b[1][1]), [r0] "v"(pa0), [r1] "v"(pa1), [t0] "v"(pb0),
+                   [t1] "v"(pb1), [o0] "i"(OB), [o1] "i"(OB + 16 * ROWB), [xa0] "v"(xa[0]), [xa1] "v"(xa[1]),
+                   [sa] "s"(sa), [ma] "s"(ma), [xb] "v"(xb[0]), [sb] "s"(sb), [mb] "s"(mb), [vm] "i"(VM)
+                 : "memory", "m0", "scc");
+  }
+};
+// The same on four blocks of columns.
+#define NT_F4(h, w)                                                                                 \
+  NT_FM("c0", "p" h w, "a" h w) NT_FM("c1", "q" h w, "a" h w)                                       \
+  NT_FM("c2", "u" h w, "a" h w) NT_FM("c3", "w" h w, "a" h w)
+template <> struct SlimPhase<float, 4> {
+  template <int OB, int VM>
+  static __device__ __forceinline__ void step(floatx4 (&c)[1][4], const u32x4 (&a)[2], const u32x4 (&b)[4][2],
+                                              u32x4 (&na)[2], u32x4 (&nb)[4][2], unsigned pa0, unsigned pa1,
+                                              unsigned pb0, unsigned pb1, const unsigned* xa, const char* sa,
+                                              unsigned ma, const unsigned* xb, const char* sb, unsigned mb) {
+    asm volatile("ds_read_b128 %[na0], %[r0]\n\tds_read_b128 %[na1], %[r1]\n\t"
+                 NT_F4("0", "0") "ds_read_b128 %[nb00], %[t0] offset:%[o0]\n\t"
+                 "ds_read_b128 %[nb01], %[t1] offset:%[o0]\n\t"
+                 NT_F4("0", "1") "ds_read_b128 %[nb10], %[t0] offset:%[o1]\n\t"
+                 "ds_read_b128 %[nb11], %[t1] offset:%[o1]\n\t"
+                 NT_F4("0", "2") "ds_read_b128 %[nb20], %[t0] offset:%[o2]\n\t"
+                 "ds_read_b128 %[nb21], %[t1] offset:%[o2]\n\t"
+                 NT_F4("0", "3") "ds_read_b128 %[nb30], %[t0] offset:%[o3]\n\t"
+                 "ds_read_b128 %[nb31], %[t1] offset:%[o3]\n\t"
+                 NT_F4("1", "0") NT_S_LD3 "s_add_u32 m0, %[mb], 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[xb1], %[sb]\n\t"
+                 NT_F4("1", "1") NT_F4("1", "2") NT_F4("1", "3") NT_END
+                 : [c0] "+v"(c[0][0]), [c1] "+v"(c[0][1]), [c2] "+v"(c[0][2]), [c3] "+v"(c[0][3]),
+                   [na0] "=&v"(na[0]), [na1] "=&v"(na[1]), [nb00] "=&v"(nb[0][0]), [nb01] "=&v"(nb[0][1]),
+                   [nb10] "=&v"(nb[1][0]), [nb11] "=&v"(nb[1][1]), [nb20] "=&v"(nb[2][0]), [nb21] "=&v"(nb[2][1]),
+                   [nb30] "=&v"(nb[3][0]), [nb31] "=&v"(nb[3][1])
+                 : NT_WORDS(a0, a[0]), NT_WORDS(a1, a[1]), NT_WORDS(p0, b[0][0]), NT_WORDS(p1, b[0][1]),
+                   NT_WORDS(q0, b[1][0]), NT_WORDS(q1, b[1][1]), NT_WORDS(u0, b[2][0]), NT_WORDS(u1, b[2][1]),
+                   NT_WORDS(w0, b[3][0]), NT_WORDS(w1, b[3][1]), [r0] "v"(pa0), [r1] "v"(pa1), [t0] "v"(pb0),
+                   [t1] "v"(pb1), [o0] "i"(OB), [o1] "i"(OB + 16 * ROWB), [o2] "i"(OB + 32 * ROWB),
+                   [o3] "i"(OB + 48 * ROWB), [xa0] "v"(xa[0]), [xa1] "v"(xa[1]), [sa] "s"(sa), [ma] "s"(ma),
+                   [xb] "v"(xb[0]), [xb1] "v"(xb[1]), [sb] "s"(sb), [mb] "s"(mb), [vm] "i"(VM)
+                 : "memory", "m0", "scc");
+  }
+};
+
+
+template <typename T, int FN, int NS, int ROLE, bool LNF>
 __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A, int lda, const void* __restrict__ Bt,
                                                         int M, int N, int K, GemmEpi epi, int tiles_m, int tiles_n) {
-  constexpr int BM = 64, BN = 32, FN = 2;
+  constexpr int BM = 64, BN = 16 * FN, LB = BN / 32;   // LB: direct loads of B per wave and k-step
   constexpr int AB = BM * ROWB, BB = BN * ROWB, SLOT = AB + BB;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * SLOT];
 
@@ -889,17 +972,19 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int fr = lane & 15, fc = lane >> 4;
 
-  // direct loads: 8 rows of 128 bytes each; two of A and one of B a wave and k-step
+  // direct loads: 8 rows of 128 bytes each
   const unsigned lda_b = (unsigned)lda * sizeof(T), ldb_b = (unsigned)K * sizeof(T);
   const unsigned ch = ((lane & 7) ^ (lane >> 3)) << 4;
   unsigned xa[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) xa[i] = (unsigned)min(m0 + (wave * 2 + i) * 8 + (lane >> 3), M - 1) * lda_b + ch;
-  const unsigned xb = (unsigned)min(n0 + wave * 8 + (lane >> 3), N - 1) * ldb_b + ch;
+  unsigned xb[LB];
+#pragma unroll
+  for (int i = 0; i < LB; ++i) xb[i] = (unsigned)min(n0 + (wave * LB + i) * 8 + (lane >> 3), N - 1) * ldb_b + ch;
   const char* Ab = reinterpret_cast<const char*>(A);
   const char* Bb = static_cast<const char*>(Bt);
   const unsigned lb = (unsigned)(uintptr_t)NT_LDS(lds);
-  const unsigned ma = lb + wave * 2048, mb = lb + AB + wave * 1024;
+  const unsigned ma = lb + wave * 2048, mb = lb + AB + wave * (LB * 1024);
   // lane addresses of the fragments in slot 0; the halves of a k-step differ in one bit
   const unsigned pa = lb + (wave * 16 + fr) * ROWB + ((fc ^ (fr & 7)) << 4);
   const unsigned pb = lb + AB + fr * ROWB + ((fc ^ (fr & 7)) << 4);
@@ -910,12 +995,13 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
     const size_t at = (size_t)min(kt, nk - 1) * ROWB;
 #pragma unroll
     for (int i = 0; i < 2; ++i) dma16(Ab + at + xa[i], lds + kt * SLOT + wave * 2048 + i * 1024);
-    dma16(Bb + at + xb, lds + kt * SLOT + AB + wave * 1024);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) dma16(Bb + at + xb[i], lds + kt * SLOT + AB + (wave * LB + i) * 1024);
   }
   floatx4 acc[1][FN];
 #pragma unroll
   for (int j = 0; j < FN; ++j) acc[0][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  constexpr int VM = (NS - 2) * 3;   // the loads behind the k-step after the next
+  constexpr int VM = (NS - 2) * (2 + LB);   // the loads behind the k-step after the next
   wait_vm<VM>();
   __builtin_amdgcn_s_barrier();
   u32x4 a0[2], a1[2], b0[FN][2], b1[FN][2];
@@ -929,13 +1015,13 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   __builtin_amdgcn_s_barrier();
   float ls = 0.f, lq = 0.f;
   T sh{};
-  if constexpr (LNF) sh = __builtin_bit_cast(T, (unsigned short)(__shfl(a0[0].x, fr, kWave) & 0xffffu));
+  if constexpr (LNF) sh = first_value<T>(__shfl(a0[0].x, fr, kWave));
 
   unsigned s0 = 0, s1 = SLOT;   // slots of this k-step and the next
   auto kstep = [&](int kt, u32x4 (&a)[2], u32x4 (&b)[FN][2], u32x4 (&na)[2], u32x4 (&nb)[FN][2]) {
     const size_t at = (size_t)min(kt + NS, nk - 1) * ROWB;
     const unsigned qa = pa + s1, qb = pb + s1;
-    SlimPhase<T>::template step<0, VM>(acc, a, b, na, nb, qa, qa ^ 64, qb, qb ^ 64, xa, Ab + at, uniform(ma + s0), xb,
+    SlimPhase<T, FN>::template step<0, VM>(acc, a, b, na, nb, qa, qa ^ 64, qb, qb ^ 64, xa, Ab + at, uniform(ma + s0), xb,
                                        Bb + at, uniform(mb + s0));
     if constexpr (LNF) {
       frag_stats<T>(a[0], sh, ls, lq);
@@ -968,10 +1054,10 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   wait_vm<0>();   // no load into LDS outlives the workgroup
 }
 
-template <typename T, int NS, int ROLE, bool LNF>
+template <typename T, int FN, int NS, int ROLE, bool LNF>
 hipError_t launch_slim(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi, hipStream_t s) {
-  const int tm = (M + 63) / 64, tn = (N + 31) / 32;
-  NT_LAUNCH((gemm_slim_kernel<T, NS, ROLE, LNF>), dim3(tm * tn), dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
+  const int tm = (M + 63) / 64, tn = (N + 16 * FN - 1) / (16 * FN);
+  NT_LAUNCH((gemm_slim_kernel<T, FN, NS, ROLE, LNF>), dim3(tm * tn), dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
             K, epi, tm, tn);
   return hipGetLastError();
 }
@@ -994,7 +1080,7 @@ hipError_t launch_tile(const void* A, int lda, const void* Bt, int M, int N, int
   } else {
     if constexpr (std::is_same<T, f16>::value)
       if (epi.wscale) return launch_phased<T, Tile128, ROLE, true, LNF>(A, lda, Bt, M, N, K, epi, s);
-    if (bm == 32) return launch_slim<T, 6, ROLE, LNF>(A, lda, Bt, M, N, K, epi, s);
+    if (bm == 32) return launch_slim<T, 2, 6, ROLE, LNF>(A, lda, Bt, M, N, K, epi, s);
     if (bm == 64) return launch_phased<T, Tile64, ROLE, false, LNF>(A, lda, Bt, M, N, K, epi, s);
     if constexpr (ROLE == 0)
       if (bm == 256) return launch_phased<T, Tile256, ROLE, false, false>(A, lda, Bt, M, N, K, epi, s);

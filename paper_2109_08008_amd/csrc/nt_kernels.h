@@ -122,6 +122,10 @@ hipError_t gemm_phased_f16(const void* A, int lda, const void* Bt, int M, int N,
 hipError_t gemm_phased_bf16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                             hipStream_t s, int role, int bm);
 
+// The phased tiles in fp32: 64 x bn, bn = 32, or 64 for encoder launches.
+hipError_t gemm_slim_f32(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
+                         hipStream_t s, int role, int bn);
+
 // The output projection's logits of chosen (row, 128-column tile) pairs, recomputed: for
 // every block of epi.gblk, the rows of its pairs times the tile's columns of Bt (N = V
 // columns in all, K = the row width), written as fp32 to out[pair][128] (columns past N

@@ -26,7 +26,7 @@ def _inputs(dtype, M, N, K, seed):
     from paper_2109_08008_amd import nt
     g = torch.Generator(device="cuda").manual_seed(seed)
     r = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
-    tdt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    tdt = {"bf16": torch.bfloat16, "f32": torch.float32}.get(dtype, torch.float16)
     a = (r(M, K) + 0.3 * r(M, 1)).to(tdt)
     w, scale = 0.1 * r(N, K), None
     if dtype == "f8":
@@ -37,7 +37,7 @@ def _inputs(dtype, M, N, K, seed):
     return a, w, scale, r(N), r(M, N).to(tdt)
 
 
-@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
 @pytest.mark.parametrize("M,N,K", [
     (1, 8, 64),            # 64x32 tiles: one row, one k-step
     (65, 100, 192),        # 64x32: two rows of tiles, an odd number of k-steps, ragged N
@@ -70,7 +70,7 @@ def test_projection_equals_small_tile(dtype, M, N, K):
         assert torch.equal(_bits(got[0]), _bits(got[1])), mode
 
 
-@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
 @pytest.mark.parametrize("M,N,K", [(3, 40, 64), (65, 1000, 448), (513, 1024, 128), (1025, 1030, 384), (2111, 3072, 256), (449, 2048, 512)])
 def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
     import torch
@@ -90,7 +90,7 @@ def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
         assert torch.equal(_bits(got[0]), _bits(got[1])), relu
 
 
-@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8"])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
 def test_batch_size_does_not_change_a_translation(dtype):
     """640 rows a step (phased tiles: cross keys/values, QKV with the cache scatter, FFN,
     the selection records) against batches of eight sentences (the small tiles)."""
