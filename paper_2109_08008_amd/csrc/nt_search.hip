@@ -282,237 +282,180 @@ __device__ __forceinline__ void list_insert(float (&v)[K2], int (&ix)[K2], float
   }
 }
 
+// Beam selection over stored logits: one workgroup a row, which it streams once.  HBM bounds
+// it (V * 4 bytes a row), so a thread keeps nothing of what it reads but its maximum and its
+// sum of exponentials: 43 registers, eight workgroups a CU, whose loads fill each other's
+// reductions.  The maxima of 64 quads of threads then give a threshold, their k2-th largest:
+// those quads hold k2 distinct logits at or above it, so the row's k2 best are at or above it
+// too.  Only the few threads whose maximum reaches it have candidates; their logits are read
+// again (one float4 a lane), what reaches the threshold is collected in LDS, and each
+// candidate counts the ones before it under (value desc, index asc).  A row with more than
+// SEL_CAP candidates (ties) is scanned again with sorted lists in each lane.  Any V and
+// alignment: single loads up to a 16-byte boundary and past the last vector.
+// k2 = 8, before (the row held in registers and sorted lists for V % 4 == 0 up to 32768, else
+// lists alone) and now: 1300 rows of 32000 57.2 -> 38.1 us (4.4 TB/s; a copy reaches 4.8), of
+// 32001 111 -> 40 us, 4000 rows 137 -> 99 us, 1 row 18.5 -> 9.1 us.  1024 threads a row
+// instead of 256: 51 us at 1300 rows and no gain at 1.
+constexpr int SEL_CAP = 512;
+
+// k2 rounds of a (value desc, index asc) wave argmax over the lanes' sorted lists; a lane's
+// head leaves its list when it is taken.
+template <int K2>
+__device__ __forceinline__ void wave_list_best(float (&v)[K2], int (&ix)[K2], int k2, int lane, float* topv,
+                                               int* topi) {
+  for (int round = 0; round < k2; ++round) {
+    float bv = v[0];
+    int bi = ix[0];
+    wave_best(bv, bi);
+    if (lane == 0) {
+      topv[round] = bi == INT_MAX ? -INFINITY : bv;
+      topi[round] = bi;
+    }
+    if (ix[0] == bi && bi != INT_MAX) {
+#pragma unroll
+      for (int j = 0; j < K2 - 1; ++j) { v[j] = v[j + 1]; ix[j] = ix[j + 1]; }
+      v[K2 - 1] = -INFINITY;
+      ix[K2 - 1] = INT_MAX;
+    }
+  }
+}
+
 template <int K2>
 __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* __restrict__ logits,
                                                                   const int* __restrict__ ctl, int beam, int V, int k2,
                                                                   float* __restrict__ topv, int* __restrict__ topi,
                                                                   float* __restrict__ lse_out) {
-  __shared__ float wv[SEL_THREADS / kWave][K2];
-  __shared__ int wi[SEL_THREADS / kWave][K2];
-  __shared__ float sm[SEL_THREADS / kWave], ss[SEL_THREADS / kWave];
+  constexpr int NT = SEL_THREADS, NW = NT / kWave;
+  static_assert(NT == 4 * 64 && NW * K2 <= SEL_CAP, "groups are quads; the candidate list holds every wave's best");
+  __shared__ float sm[NW], ss[NW], cand_v[SEL_CAP];
+  __shared__ float4 gmax[16];
+  __shared__ int cand_i[SEL_CAP], cnt;
   const int r = blockIdx.x;
   if (ctl && r >= ctl[CTL_NLIVE] * beam) return;
   const float* x = logits + (size_t)r * V;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-
-  // one pass over the row: online max/sum for the LSE and a sorted list of this
-  // thread's K2 largest logits (elements visited in increasing index)
-  MaxSum acc{-INFINITY, 0.f};
-  float v[K2];
-  int ix[K2];
-#pragma unroll
-  for (int j = 0; j < K2; ++j) { v[j] = -INFINITY; ix[j] = INT_MAX; }
-  const bool vec = (V % 4) == 0 && ((reinterpret_cast<uintptr_t>(x) & 15) == 0);
-  if (vec) {
-    // SEL_BATCH loads of a thread are issued together before any is used (one memory
-    // latency per batch instead of per element group)
-    const float4* x4 = reinterpret_cast<const float4*>(x);
-    const int nv = V / 4;
-    for (int i0 = tid; i0 < nv; i0 += SEL_THREADS * SEL_BATCH) {
-      float4 qs[SEL_BATCH];
-#pragma unroll
-      for (int u = 0; u < SEL_BATCH; ++u) {
-        const int i = i0 + u * SEL_THREADS;
-        qs[u] = i < nv ? x4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-      }
-#pragma unroll
-      for (int u = 0; u < SEL_BATCH; ++u) {
-        const int i = i0 + u * SEL_THREADS;
-        const float4 q = qs[u];
-        const float mx = fmaxf(fmaxf(q.x, q.y), fmaxf(q.z, q.w));
-        if (mx > acc.m) {
-          acc.s = acc.m == -INFINITY ? 0.f : acc.s * __expf(acc.m - mx);
-          acc.m = mx;
-        }
-        if (i < nv) acc.s += __expf(q.x - acc.m) + __expf(q.y - acc.m) + __expf(q.z - acc.m) + __expf(q.w - acc.m);
-        if (mx > v[K2 - 1]) {
-          list_insert<K2>(v, ix, q.x, 4 * i);
-          list_insert<K2>(v, ix, q.y, 4 * i + 1);
-          list_insert<K2>(v, ix, q.z, 4 * i + 2);
-          list_insert<K2>(v, ix, q.w, 4 * i + 3);
-        }
-      }
-    }
-  } else {
-    for (int i = tid; i < V; i += SEL_THREADS) {
-      const float q = x[i];
-      if (q > acc.m) {
-        acc.s = acc.m == -INFINITY ? 0.f : acc.s * __expf(acc.m - q);
-        acc.m = q;
-      }
-      acc.s += __expf(q - acc.m);
-      list_insert<K2>(v, ix, q, i);
-    }
+  if (tid == 0) cnt = 0;
+  // the row as `head` single logits up to a 16-byte boundary, nv vectors and a tail; threads
+  // 0..3 take the head's, 4..7 the tail's
+  const int head = min(V, (int)((16 - (reinterpret_cast<uintptr_t>(x) & 15)) & 15) / 4);
+  const int nv = (V - head) / 4;
+  const float4* x4 = reinterpret_cast<const float4*>(x + head);
+  const int single = tid < 4 ? (tid < head ? tid : -1) : tid < 8 && head + 4 * nv + tid - 4 < V ? head + 4 * nv + tid - 4 : -1;
+  float m = -INFINITY, sum = 0.f;
+  if (single >= 0) {
+    const float c = x[single];
+    m = fmaxf(c, -INFINITY);
+    sum = c == -INFINITY ? 0.f : __expf(c - c);   // 1; NaN of an infinity or a NaN
   }
-  acc = wave_ms(acc);
+  for (int i0 = tid; i0 < nv; i0 += NT * SEL_BATCH) {
+    float4 q[SEL_BATCH];
+#pragma unroll
+    for (int u = 0; u < SEL_BATCH; ++u) {
+      const int i = i0 + u * NT;
+      q[u] = i < nv ? x4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < SEL_BATCH; ++u) mx = fmaxf(mx, fmaxf(fmaxf(q[u].x, q[u].y), fmaxf(q[u].z, q[u].w)));
+    if (m != -INFINITY) sum *= __expf(m - mx);
+    m = mx;
+    // a batch of -inf only adds nothing (and a NaN among them shows in the sum)
+    const float ref = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+    for (int u = 0; u < SEL_BATCH; ++u)
+      sum += (__expf(q[u].x - ref) + __expf(q[u].y - ref)) + (__expf(q[u].z - ref) + __expf(q[u].w - ref));
+  }
+  const MaxSum acc = wave_ms(MaxSum{m, sum});
   if (lane == 0) { sm[wave] = acc.m; ss[wave] = acc.s; }
-
-  // each wave merges its 64 lists: K2 rounds of a wave-wide (value desc, index asc) argmax;
-  // the winning lane drops its head
-  for (int round = 0; round < K2; ++round) {
-    float bv = v[0];
-    int bi = ix[0];
-    wave_best(bv, bi);
-    if (lane == 0) { wv[wave][round] = bv; wi[wave][round] = bi; }
-    if (ix[0] == bi && v[0] == bv && bi != INT_MAX) {
-#pragma unroll
-      for (int j = 0; j < K2 - 1; ++j) { v[j] = v[j + 1]; ix[j] = ix[j + 1]; }
-      v[K2 - 1] = -INFINITY;
-      ix[K2 - 1] = INT_MAX;
-    }
-  }
+  float g = fmaxf(m, dpp_mov<DPP_XOR1>(m));
+  g = fmaxf(g, dpp_mov<DPP_XOR2>(g));
+  if (tid % 4 == 0) reinterpret_cast<float*>(gmax)[tid / 4] = g;
   __syncthreads();
-  if (tid == 0) {
-    int head[SEL_THREADS / kWave] = {0, 0, 0, 0};
-    for (int j = 0; j < k2; ++j) {
-      int w = 0;
-      float bv = -INFINITY;
-      int bi = INT_MAX;
-      for (int q = 0; q < SEL_THREADS / kWave; ++q) {
-        if (head[q] >= K2 || wi[q][head[q]] == INT_MAX) continue;     // list exhausted
-        if (bi == INT_MAX || better(wv[q][head[q]], wi[q][head[q]], bv, bi)) {
-          bv = wv[q][head[q]]; bi = wi[q][head[q]]; w = q;
-        }
+  // The k2-th largest group maximum, in each wave: lane j counts the maxima before group j's
+  // (a NaN cannot be one).
+  const float mine = reinterpret_cast<const float*>(gmax)[lane];
+  int before = 0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const float4 o = gmax[j];
+    before += better(o.x, 4 * j, mine, lane) + better(o.y, 4 * j + 1, mine, lane) +
+              better(o.z, 4 * j + 2, mine, lane) + better(o.w, 4 * j + 3, mine, lane);
+  }
+  const float thr = readlane_f(mine, __builtin_ctzll(__ballot(before == k2 - 1)));
+  auto take = [&](float c, int i) {
+    if (c >= thr && c != -INFINITY) {
+      const int at = atomicAdd(&cnt, 1);
+      if (at < SEL_CAP) {
+        cand_v[at] = c;
+        cand_i[at] = i;
       }
-      head[w]++;
-      topv[(size_t)r * k2 + j] = bv;
-      topi[(size_t)r * k2 + j] = bi;
     }
-    MaxSum tot{sm[0], ss[0]};
-#pragma unroll
-    for (int w = 1; w < SEL_THREADS / kWave; ++w) tot = ms_merge(tot, MaxSum{sm[w], ss[w]});
-    lse_out[r] = tot.m + logf(tot.s);
-  }
-}
-
-// Beam selection for rows of at most SEL_THREADS * 4 * SEL_REG logits, held in registers:
-// pass 1 forms the online (max, sum exp) and each thread's maximum; the K2-th largest
-// thread maximum is a threshold that every one of the row's K2 best logits reaches (the
-// K2 largest thread maxima are K2 distinct logits at or above it); pass 2 inserts only
-// logits at or above it into the thread lists, which are then merged as in
-// beam_select_kernel.  Same result, without a list insertion for most logits.
-constexpr int SEL_REG = 32;        // float4 per thread -> rows up to 32768 logits
-template <int K2>
-__global__ __launch_bounds__(SEL_THREADS) void beam_select_reg_kernel(const float* __restrict__ logits,
-                                                                      const int* __restrict__ ctl, int beam, int V,
-                                                                      int k2, float* __restrict__ topv,
-                                                                      int* __restrict__ topi,
-                                                                      float* __restrict__ lse_out) {
-  __shared__ float wv[SEL_THREADS / kWave][K2];
-  __shared__ int wi[SEL_THREADS / kWave][K2];
-  __shared__ float sm[SEL_THREADS / kWave], ss[SEL_THREADS / kWave];
-  __shared__ float wmax[SEL_THREADS / kWave][K2];
-  __shared__ float thr_s;
-  const int r = blockIdx.x;
-  if (ctl && r >= ctl[CTL_NLIVE] * beam) return;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const float4* x4 = reinterpret_cast<const float4*>(logits + (size_t)r * V);
-  const int nv = V / 4;
-  float4 q[SEL_REG];
-#pragma unroll
-  for (int u = 0; u < SEL_REG; ++u) {
-    const int i = tid + u * SEL_THREADS;
-    q[u] = i < nv ? x4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-  }
-  // pass 1: thread maximum, then the sum of exp against it
-  float tmax = -INFINITY;
-#pragma unroll
-  for (int u = 0; u < SEL_REG; ++u) tmax = fmaxf(tmax, fmaxf(fmaxf(q[u].x, q[u].y), fmaxf(q[u].z, q[u].w)));
-  MaxSum acc{tmax, 0.f};
-  if (tmax != -INFINITY) {
-#pragma unroll
-    for (int u = 0; u < SEL_REG; ++u)
-      acc.s += (__expf(q[u].x - tmax) + __expf(q[u].y - tmax)) + (__expf(q[u].z - tmax) + __expf(q[u].w - tmax));
-  }
-  acc = wave_ms(acc);
-  if (lane == 0) { sm[wave] = acc.m; ss[wave] = acc.s; }
-  // the K2 largest thread maxima of each wave (K2 rounds of a wave max; one lane drops out)
-  {
-    float mine = tmax;
-    for (int j = 0; j < K2; ++j) {
-      float best = mine;
-      int bl = lane;
-      wave_best(best, bl);
-      if (lane == 0) wmax[wave][j] = best;
-      if (lane == bl) mine = -INFINITY;
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    // K2-th largest of the per-wave sorted lists
-    int head[SEL_THREADS / kWave] = {0, 0, 0, 0};
-    float t = -INFINITY;
-    for (int j = 0; j < K2; ++j) {
-      int w = 0;
-      float bv = -INFINITY;
-      for (int q2 = 0; q2 < SEL_THREADS / kWave; ++q2)
-        if (head[q2] < K2 && (wmax[q2][head[q2]] > bv || w < 0)) { bv = wmax[q2][head[q2]]; w = q2; }
-      head[w]++;
-      t = bv;
-    }
-    thr_s = t;
-  }
-  __syncthreads();
-  const float thr = thr_s;
-  // pass 2: bit masks of the logits at or above the threshold (bit 4*(u%8)+c of word u/8),
-  // then the few candidates go into the thread list in increasing index order, re-read
-  // from memory (the register copy cannot be indexed by a run-time position)
-  unsigned cand[SEL_REG / 8] = {};
-#pragma unroll
-  for (int u = 0; u < SEL_REG; ++u) {
-    const float4 x = q[u];
-    const unsigned bits = (x.x >= thr ? 1u : 0u) | (x.y >= thr ? 2u : 0u) | (x.z >= thr ? 4u : 0u) |
-                          (x.w >= thr ? 8u : 0u);
-    if (tid + u * SEL_THREADS < nv) cand[u / 8] |= bits << (4 * (u % 8));   // padding never re-read
-  }
-  float v[K2];
-  int ix[K2];
-#pragma unroll
-  for (int j = 0; j < K2; ++j) { v[j] = -INFINITY; ix[j] = INT_MAX; }
-  const float* row = logits + (size_t)r * V;
-#pragma unroll
-  for (int wd = 0; wd < SEL_REG / 8; ++wd) {
-    unsigned m = cand[wd];
-    while (m) {
-      const int b = __builtin_ctz(m);
-      m &= m - 1;
-      const int idx = 4 * (tid + (wd * 8 + b / 4) * SEL_THREADS) + (b & 3);
-      list_insert<K2>(v, ix, row[idx], idx);
-    }
-  }
-  // merge: per wave K2 rounds of a (value desc, index asc) argmax, then thread 0 over waves
-  for (int round = 0; round < K2; ++round) {
-    float bv = v[0];
-    int bi = ix[0];
-    wave_best(bv, bi);
-    if (lane == 0) { wv[wave][round] = bv; wi[wave][round] = bi; }
-    if (ix[0] == bi && v[0] == bv && bi != INT_MAX) {
-#pragma unroll
-      for (int j = 0; j < K2 - 1; ++j) { v[j] = v[j + 1]; ix[j] = ix[j + 1]; }
-      v[K2 - 1] = -INFINITY;
-      ix[K2 - 1] = INT_MAX;
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int head[SEL_THREADS / kWave] = {0, 0, 0, 0};
-    for (int j = 0; j < k2; ++j) {
-      int w = 0;
-      float bv = -INFINITY;
-      int bi = INT_MAX;
-      for (int q2 = 0; q2 < SEL_THREADS / kWave; ++q2) {
-        if (head[q2] >= K2 || wi[q2][head[q2]] == INT_MAX) continue;
-        if (bi == INT_MAX || better(wv[q2][head[q2]], wi[q2][head[q2]], bv, bi)) {
-          bv = wv[q2][head[q2]]; bi = wi[q2][head[q2]]; w = q2;
-        }
+  };
+  if (single >= 0 && m >= thr) take(x[single], single);
+  unsigned long long who = __ballot(m >= thr && m != -INFINITY);
+  while (who && *(volatile int*)&cnt <= SEL_CAP) {
+    // two of the wave's candidate threads at a time: lane u reads their vectors u, u + 64, ..
+    const int l0 = __builtin_ctzll(who);
+    who &= who - 1;
+    const int l1 = who ? __builtin_ctzll(who) : -1;
+    who &= who - 1;   // (0 stays 0)
+    for (int u = lane; u * NT < nv; u += kWave) {
+      const int i0 = wave * kWave + l0 + u * NT, i1 = wave * kWave + l1 + u * NT;
+      const bool h0 = i0 < nv, h1 = l1 >= 0 && i1 < nv;
+      const float4 a = x4[h0 ? i0 : 0], b = x4[h1 ? i1 : 0];
+      if (h0) {
+        take(a.x, head + 4 * i0);
+        take(a.y, head + 4 * i0 + 1);
+        take(a.z, head + 4 * i0 + 2);
+        take(a.w, head + 4 * i0 + 3);
       }
-      head[w]++;
-      topv[(size_t)r * k2 + j] = bv;
-      topi[(size_t)r * k2 + j] = bi;
+      if (h1) {
+        take(b.x, head + 4 * i1);
+        take(b.y, head + 4 * i1 + 1);
+        take(b.z, head + 4 * i1 + 2);
+        take(b.w, head + 4 * i1 + 3);
+      }
     }
-    MaxSum tot{sm[0], ss[0]};
+  }
+  __syncthreads();
+  int n = cnt;
+  if (n > SEL_CAP) {   // every wave's k2 best of its part of the row are the candidates
+    float v[K2];
+    int ix[K2];
 #pragma unroll
-    for (int w = 1; w < SEL_THREADS / kWave; ++w) tot = ms_merge(tot, MaxSum{sm[w], ss[w]});
+    for (int j = 0; j < K2; ++j) { v[j] = -INFINITY; ix[j] = INT_MAX; }
+    for (int i0 = tid; i0 < V; i0 += NT * SEL_BATCH) {
+      float q[SEL_BATCH];
+#pragma unroll
+      for (int u = 0; u < SEL_BATCH; ++u) q[u] = i0 + u * NT < V ? x[i0 + u * NT] : -INFINITY;
+#pragma unroll
+      for (int u = 0; u < SEL_BATCH; ++u) list_insert<K2>(v, ix, q[u], i0 + u * NT);
+    }
+    wave_list_best<K2>(v, ix, k2, lane, cand_v + wave * k2, cand_i + wave * k2);
+    n = NW * k2;
+    __syncthreads();
+  }
+  // a candidate's place is the number of candidates before it (they are distinct, but for the
+  // empty ones a wave may have left, index INT_MAX)
+  topv += (size_t)r * k2;
+  topi += (size_t)r * k2;
+  for (int e = tid; e < n; e += NT) {
+    const float c = cand_v[e];
+    const int i = cand_i[e];
+    int at = 0;
+    for (int j = 0; j < n; ++j) at += better(cand_v[j], cand_i[j], c, i);
+    if (at < k2 && i != INT_MAX) {
+      topv[at] = c;
+      topi[at] = i;
+    }
+  }
+  if (tid >= n && tid < k2) {   // fewer finite logits than k2
+    topv[tid] = -INFINITY;
+    topi[tid] = INT_MAX;
+  }
+  if (tid == 0) {
+    MaxSum tot{sm[0], ss[0]};
+    for (int w = 1; w < NW; ++w) tot = ms_merge(tot, MaxSum{sm[w], ss[w]});
     lse_out[r] = tot.m + logf(tot.s);
   }
 }
@@ -1201,19 +1144,9 @@ hipError_t greedy_step_fused(const float* part, int n_tiles, const SearchState& 
 hipError_t beam_select(const float* logits, const int* ctl, int beam, int rows, int V, int k2, float* topv, int* topi,
                        float* lse, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  const bool reg = (V % 4) == 0 && V <= SEL_THREADS * 4 * SEL_REG && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
-  if (reg && k2 <= 8) {
-    if (k2 <= 4) NT_LAUNCH(beam_select_reg_kernel<4>, dim3(rows), dim3(SEL_THREADS), 0, s, logits, ctl, beam, V, k2,
-                           topv, topi, lse);
-    else NT_LAUNCH(beam_select_reg_kernel<8>, dim3(rows), dim3(SEL_THREADS), 0, s, logits, ctl, beam, V, k2, topv,
-                   topi, lse);
-    return hipGetLastError();
-  }
-#define NT_SEL(K2)                                                                                          \
-  NT_LAUNCH(beam_select_kernel<K2>, dim3(rows), dim3(SEL_THREADS), 0, s, logits, ctl, beam, V, k2, topv, \
-                     topi, lse)
-  if (k2 <= 4) NT_SEL(4);
-  else if (k2 <= 8) NT_SEL(8);
+#define NT_SEL(K2) \
+  NT_LAUNCH(beam_select_kernel<K2>, dim3(rows), dim3(SEL_THREADS), 0, s, logits, ctl, beam, V, k2, topv, topi, lse)
+  if (k2 <= 8) NT_SEL(8);
   else if (k2 <= 16) NT_SEL(16);
   else if (k2 <= 32) NT_SEL(32);
   else return hipErrorInvalidValue;

@@ -3,8 +3,8 @@ row's log-sum-exp) against NumPy, through nt_op_select (a scan of the whole row)
 nt_op_select_tiled (from per-128-column-tile records, reading back only the tiles that
 can hold one of the k largest).
 
-Covers the register-resident kernel (V % 4 == 0, V <= 32768) and the streaming kernel
-(other V), heavy ties (values drawn from a few integers, equal rows -- many tiles then
+Covers rows that start at any alignment (V % 4 != 0), more candidates than the selection
+collects, heavy ties (values drawn from a few integers, equal rows -- many tiles then
 share the k-th largest maximum), a row whose maximum is its last logit, -inf logits
 (never selected; whole tiles of -inf), V below one tile and not a multiple of it, and k
 up to 32.
@@ -78,3 +78,31 @@ def test_select_matches_numpy(V, kind, entry):
         fin = np.isfinite(el)
         np.testing.assert_allclose(ls[fin], el[fin], rtol=2e-6, atol=2e-5)
         assert np.array_equal(np.isfinite(ls), fin)
+
+
+@pytest.mark.parametrize("V", [1, 2, 3, 4, 5, 255, 1021, 1026, 2051, 8195])
+@pytest.mark.parametrize("kind", ["normal", "ties", "steps"])
+def test_select_stored_edges(V, kind):
+    """The streamed row: heads and tails of 0 to 3 single logits (rows of odd V start at every
+    alignment), rows shorter than a vector or than one load per thread, and "steps", where one
+    thread in four holds the row's k largest and a plateau of more ties than the candidate list
+    takes follows.  Selection is exact; the log-sum-exp is held to 4 ulp of its own size plus the
+    error of V rounded terms (V * 2**-24 relative in the sum at the very worst)."""
+    rows = 9
+    if kind == "steps":
+        x = np.zeros((rows, V), dtype=np.float32)
+        x[:, :: 16] = 1.0
+        x[:, V // 2] = 2.0
+        x[4:, V // 3:] = -np.inf
+    else:
+        x = _logits(V, rows, kind, seed=3 * V)
+    for k in (1, 3, 8, 13, 32):
+        if k > V:
+            continue
+        tv, ti, ls = _run(x, k)
+        ev, ei, el = _expected(x, k)
+        np.testing.assert_array_equal(ti, ei, err_msg=f"k={k}")
+        np.testing.assert_array_equal(tv, ev, err_msg=f"k={k}")
+        fin = np.isfinite(el)
+        assert np.array_equal(np.isfinite(ls), fin)
+        assert np.all(np.abs(ls[fin] - el[fin]) <= 2.0 ** -21 * (1 + np.abs(el[fin])) + V * 2.0 ** -24)
