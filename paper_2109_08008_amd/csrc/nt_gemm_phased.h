@@ -282,11 +282,64 @@ __device__ __forceinline__ void mode_switch(int mode, F& f) {
 // The epilogue of a wave's FM x FN blocks: lane (fr, fc) holds columns nw + 16 j + 4 fc .. + 3 of
 // the rows mw + 16 i + fr.  mu, rs: the rows' statistics (folded LayerNorm); cs: LDS of the
 // wave's own for half its rows in fp32, ln_mu / ln_rs the statistics of all its rows in LDS.
+// A word that no block of this launch writes, through the scalar cache.
+__device__ __forceinline__ int scalar_int(const int* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// What the epilogue of a whole, aligned tile of one block row adds, read before the k-loop: at
+// the few k-steps of a small product these loads, one after another behind the last MFMA, are
+// a fifth of its time.
+template <int FN>
+struct EpiAhead {
+  float4 bias[FN];
+  floatx4 colsum[FN];
+  uint4 resid[FN];      // 16-bit: [FN / 2] used
+  int sent = 0;
+  bool on = false;
+};
+template <typename T, int FN, int ROLE, bool LNF>
+__device__ __forceinline__ void epi_ahead(EpiAhead<FN>& e, const GemmEpi& epi, int M, int mw, int nw, int fr, int fc) {
+  const int m = min(mw + fr, M - 1);
+  if constexpr (LNF) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) e.colsum[j] = *reinterpret_cast<const floatx4*>(epi.lnf_colsum + nw + j * 16 + 4 * fc);
+  }
+  if (epi.bias) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) e.bias[j] = *reinterpret_cast<const float4*>(epi.bias + nw + j * 16 + 4 * fc);
+  }
+  if (epi.mode == EPI_RESID) {
+    const T* r = static_cast<const T*>(epi.resid) + (size_t)m * epi.ldc + nw;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+      for (int jp = 0; jp < FN / 2; ++jp)
+        e.resid[jp] = *reinterpret_cast<const uint4*>(r + jp * 32 + (fc & 1) * 16 + (fc >> 1) * 8);
+    } else {
+#pragma unroll
+      for (int j = 0; j < FN; ++j) e.resid[j] = *reinterpret_cast<const uint4*>(r + j * 16 + 4 * fc);
+    }
+  }
+  if constexpr (ROLE == 1) {
+    if (epi.mode == EPI_SELF_QKV) e.sent = epi.sent_list[m / epi.beam];
+  }
+}
+template <typename T, bool F8, bool LNF>
+__device__ __forceinline__ bool epi_whole(const GemmEpi& epi, int nw, int cols, int N) {
+  const bool f32_out = epi.mode <= EPI_STORE || epi.mode == EPI_TOPK ? epi.out_f32 : 0;
+  uintptr_t al = reinterpret_cast<uintptr_t>(epi.bias);
+  if (epi.mode != EPI_CROSS_KV) al |= reinterpret_cast<uintptr_t>(epi.out) | ((uintptr_t)epi.ldc * (f32_out ? 4 : sizeof(T)));
+  if (epi.mode == EPI_RESID) al |= reinterpret_cast<uintptr_t>(epi.resid);
+  if (F8) al |= reinterpret_cast<uintptr_t>(epi.wscale);
+  if (LNF) al |= reinterpret_cast<uintptr_t>(epi.lnf_colsum);
+  return nw + cols <= N && (al & 15) == 0;
+}
+
 template <typename T, int FM, int FN, int ROLE, bool F8, bool LNF>
 __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const GemmEpi& epi, int M, int N, int mw, int nw,
                                                 int t_slot, int fr, int fc, const float (&mu)[FM],
                                                 const float (&rs)[FM], float* cs, const float* ln_mu,
-                                                const float* ln_rs) {
+                                                const float* ln_rs, const EpiAhead<FN>& ahead) {
   using std::integral_constant;
 
   if constexpr (ROLE == 2) {
@@ -342,14 +395,7 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
     }
   }
 
-  const bool f32_out = epi.mode <= EPI_STORE || epi.mode == EPI_TOPK ? epi.out_f32 : 0;
-  uintptr_t al = reinterpret_cast<uintptr_t>(epi.bias);
-  if (epi.mode != EPI_CROSS_KV) al |= reinterpret_cast<uintptr_t>(epi.out) | ((uintptr_t)epi.ldc * (f32_out ? 4 : sizeof(T)));
-  if (epi.mode == EPI_RESID) al |= reinterpret_cast<uintptr_t>(epi.resid);
-  if (F8) al |= reinterpret_cast<uintptr_t>(epi.wscale);
-  if (LNF) al |= reinterpret_cast<uintptr_t>(epi.lnf_colsum);
-
-  if (nw + FN * 16 > N || (al & 15) != 0) {
+  if (FM == 1 ? !ahead.on : !epi_whole<T, F8, LNF>(epi, nw, FN * 16, N)) {
     if constexpr (FM == 1) {   // a ragged or unaligned tile, four columns at a time
       auto finish = [&](auto mode_c) {
         constexpr int MODE = decltype(mode_c)::value;
@@ -420,7 +466,8 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
     for (int j = 0; j < FN; ++j) {
       const int n = nw + j * 16 + 4 * fc;
       floatx4 c4{}, w4{};
-      if constexpr (LNF) c4 = *reinterpret_cast<const floatx4*>(epi.lnf_colsum + n);
+      if constexpr (LNF && FM == 1) c4 = ahead.colsum[j];
+      else if constexpr (LNF) c4 = *reinterpret_cast<const floatx4*>(epi.lnf_colsum + n);
       if constexpr (F8) w4 = *reinterpret_cast<const floatx4*>(epi.wscale + n);
 #pragma unroll
       for (int i = 0; i < FM; ++i)
@@ -438,8 +485,10 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
     constexpr int MODE = decltype(mode_c)::value;
     float4 b4[FN];
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-      b4[j] = epi.bias ? *reinterpret_cast<const float4*>(epi.bias + nw + j * 16 + 4 * fc) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < FN; ++j) {
+      if constexpr (FM == 1) b4[j] = ahead.bias[j];
+      else b4[j] = epi.bias ? *reinterpret_cast<const float4*>(epi.bias + nw + j * 16 + 4 * fc) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     constexpr bool RES = MODE == EPI_RESID && sizeof(T) == 2;
     uint4 res[RES ? FM : 1][RES ? FN / 2 : 1];
     if constexpr (RES) {   // every residual before the first store (the output may alias it)
@@ -447,7 +496,10 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
       for (int i = 0; i < FM; ++i) {
         const T* r = static_cast<const T*>(epi.resid) + (size_t)min(mw + i * 16 + fr, M - 1) * epi.ldc + nw + n8;
 #pragma unroll
-        for (int jp = 0; jp < FN / 2; ++jp) res[i][jp] = *reinterpret_cast<const uint4*>(r + jp * 32);
+        for (int jp = 0; jp < FN / 2; ++jp) {
+          if constexpr (FM == 1) res[i][jp] = ahead.resid[jp];
+          else res[i][jp] = *reinterpret_cast<const uint4*>(r + jp * 32);
+        }
       }
     }
 #pragma unroll
@@ -460,7 +512,7 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
       }
       if constexpr (MODE == EPI_SELF_QKV) {
         const int mc = min(m, M - 1);
-        const int p = epi.sent_list[mc / epi.beam] * epi.beam + mc % epi.beam;
+        const int p = (FM == 1 ? ahead.sent : epi.sent_list[mc / epi.beam]) * epi.beam + mc % epi.beam;
         cell = ((size_t)p * epi.H * epi.Tcap + t_slot) * epi.dh;
       }
       if constexpr (MODE == EPI_CROSS_KV) {
@@ -519,7 +571,8 @@ __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const Gemm
           for (int u = 0; u < 2; ++u) {
             const int nu = n + u * 16 + 4 * fc;
             if constexpr (MODE == EPI_RESID) {
-              const floatx4 q = *reinterpret_cast<const floatx4*>(static_cast<const float*>(epi.resid) + row + nu);
+              static_assert(FM == 1, "fp32 tiles are one block row");
+              const floatx4 q = __builtin_bit_cast(floatx4, ahead.resid[2 * jp + u]);
 #pragma unroll
               for (int r = 0; r < 4; ++r) v[u][r] += q[r];
             }
@@ -822,7 +875,7 @@ __global__ __launch_bounds__(W::WGM * W::WGN * kWave, 2) void gemm_phased_kernel
   }
   phased_epilogue<T, FM, FN, ROLE, F8, LNF>(acc, epi, M, N, m0 + wm * (FM * 16), n0 + wn * (FN * 16), t_slot, fr, fc, mu,
                                             rs, reinterpret_cast<float*>(lds) + wave * (HROWS * CS),
-                                            ln_mu + wm * (FM * 16), ln_rs + wm * (FM * 16));
+                                            ln_mu + wm * (FM * 16), ln_rs + wm * (FM * 16), EpiAhead<FN>{});
 }
 
 // ---- few tiles: 64x32, one phase a k-step ----------------------------------------------------
@@ -947,26 +1000,35 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   constexpr int AB = BM * ROWB, BB = BN * ROWB, SLOT = AB + BB;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * SLOT];
 
-  asm volatile("" ::"s"(epi.ctl), "s"(epi.bias), "s"(epi.out), "s"(epi.ldc), "s"(epi.wscale), "s"(epi.part),
-               "s"(tiles_n), "s"(M), "s"(Bt));
-  if (epi.ctl) {
-    M = min(M, epi.ctl[CTL_NLIVE] * epi.ctl_rows);
-    tiles_m = (M + BM - 1) / BM;
-  }
-  const int ntiles = tiles_m * tiles_n;
-  int pid = blockIdx.x;
-  if (pid >= ntiles) return;
-  {
+  // every argument the k-loop needs in one round of scalar loads
+  asm volatile("" ::"s"(epi.ctl), "s"(epi.bias), "s"(epi.out), "s"(epi.ldc), "s"(epi.mode), "s"(epi.resid),
+               "s"(epi.lnf_colsum), "s"(epi.sent_list), "s"(epi.beam), "s"(epi.ctl_rows), "s"(A), "s"(lda), "s"(K),
+               "s"(N), "s"(M), "s"(Bt), "s"(tiles_n));
+  // A decoder step's tiles do not depend on how many rows are live (the grid's y is the tile row,
+  // an XCD owns a panel of columns), so their first loads are under way before the count is
+  // known; rows past the live ones are rows of the same buffers.
+  int tm, tn, n_live = 0, t_slot = 0;
+  if constexpr (ROLE == 1) {
+    const int* ctl = epi.ctl ? epi.ctl : reinterpret_cast<const int*>(A);   // (no branch to wait in)
+    n_live = scalar_int(ctl + CTL_NLIVE);
+    t_slot = scalar_int(ctl + CTL_T);
+    tm = blockIdx.y;
+    tn = blockIdx.x % 8 * ((tiles_n + 7) / 8) + blockIdx.x / 8;
+    if (tn >= tiles_n) return;
+  } else {
+    // XCD-contiguous, then grouped by 8 tile-rows
+    const int ntiles = tiles_m * tiles_n;
+    int pid = blockIdx.x;
     const int q = ntiles / 8, r = ntiles % 8, xcd = pid % 8, idx = pid / 8;
     pid = xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+    constexpr int GROUP = 8;
+    const int per_group = GROUP * tiles_n;
+    const int first_m = (pid / per_group) * GROUP;
+    const int gsize = min(tiles_m - first_m, GROUP);
+    tm = first_m + (pid % per_group) % gsize;
+    tn = (pid % per_group) / gsize;
   }
-  constexpr int GROUP = 8;
-  const int per_group = GROUP * tiles_n;
-  const int first_m = (pid / per_group) * GROUP;
-  const int gsize = min(tiles_m - first_m, GROUP);
-  const int tm = first_m + (pid % per_group) % gsize, tn = (pid % per_group) / gsize;
   const int m0 = tm * BM, n0 = tn * BN;
-  const int t_slot = epi.ctl ? epi.ctl[CTL_T] : epi.t;
 
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -990,14 +1052,30 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   const unsigned pb = lb + AB + fr * ROWB + ((fc ^ (fr & 7)) << 4);
 
   const int nk = (int)((size_t)K * sizeof(T) / ROWB);
-#pragma unroll
-  for (int kt = 0; kt < NS; ++kt) {   // past the last k-step: its bytes again, never read
+  auto fill = [&](int kt) {   // past the last k-step: its bytes again, never read
     const size_t at = (size_t)min(kt, nk - 1) * ROWB;
 #pragma unroll
     for (int i = 0; i < 2; ++i) dma16(Ab + at + xa[i], lds + kt * SLOT + wave * 2048 + i * 1024);
 #pragma unroll
     for (int i = 0; i < LB; ++i) dma16(Bb + at + xb[i], lds + kt * SLOT + AB + (wave * LB + i) * 1024);
+  };
+  fill(0);
+  fill(1);
+  int live = M;
+  if constexpr (ROLE == 1) {
+    asm volatile("" : "+s"(n_live), "+s"(t_slot));
+    if (epi.ctl) live = min(M, n_live * epi.ctl_rows);
+    else t_slot = epi.t;
+    if (m0 >= live) {   // no load into LDS outlives the workgroup
+      wait_vm<0>();
+      return;
+    }
   }
+  EpiAhead<FN> ahead{};
+  ahead.on = epi_whole<T, false, LNF>(epi, n0, BN, N);
+  if (ahead.on) epi_ahead<T, FN, ROLE, LNF>(ahead, epi, M, m0 + wave * 16, n0, fr, fc);
+#pragma unroll
+  for (int kt = 2; kt < NS; ++kt) fill(kt);
   floatx4 acc[1][FN];
 #pragma unroll
   for (int j = 0; j < FN; ++j) acc[0][j] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1049,15 +1127,16 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
     mu[0] = to_f32(sh) + ms;
     rs[0] = 1.0f / sqrtf(var + epi.lnf_eps);
   }
-  phased_epilogue<T, 1, FN, ROLE, false, LNF>(acc, epi, M, N, m0 + wave * 16, n0, t_slot, fr, fc, mu, rs, nullptr,
-                                              nullptr, nullptr);
+  phased_epilogue<T, 1, FN, ROLE, false, LNF>(acc, epi, live, N, m0 + wave * 16, n0, t_slot, fr, fc, mu, rs, nullptr,
+                                              nullptr, nullptr, ahead);
   wait_vm<0>();   // no load into LDS outlives the workgroup
 }
 
 template <typename T, int FN, int NS, int ROLE, bool LNF>
 hipError_t launch_slim(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi, hipStream_t s) {
   const int tm = (M + 63) / 64, tn = (N + 16 * FN - 1) / (16 * FN);
-  NT_LAUNCH((gemm_slim_kernel<T, FN, NS, ROLE, LNF>), dim3(tm * tn), dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
+  const dim3 grid = ROLE == 1 ? dim3((tn + 7) / 8 * 8, tm) : dim3(tm * tn);
+  NT_LAUNCH((gemm_slim_kernel<T, FN, NS, ROLE, LNF>), grid, dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
             K, epi, tm, tn);
   return hipGetLastError();
 }
