@@ -320,8 +320,10 @@ constexpr int SELECT_NOALLOC_MAX_RECORDS = 1 << 20;   // 16 MiB
 hipError_t select_scratch(float** out, size_t* records);
 
 // Fused greedy selection after an EPI_TOPK projection (k2 = 1): merges the per-tile
-// partials of each live row into the argmax and the LSE, then the greedy update.
-hipError_t greedy_step_fused(const float* part, int n_tiles, const SearchState& st, hipStream_t s);
+// partials of each live row into the argmax and the LSE, then the greedy update.  forced (may
+// be null) gives each sentence's token instead; it needs logits, the stored [B][V] logits.
+hipError_t greedy_step_fused(const float* part, int n_tiles, const float* logits, const int* forced,
+                             const SearchState& st, hipStream_t s);
 
 // End of a decode step (one workgroup): counts the unfinished sentences of the live list,
 // drops the finished ones in place when pruning, advances t, flips the ancestor half

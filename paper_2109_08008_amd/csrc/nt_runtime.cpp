@@ -930,11 +930,14 @@ nt_status enqueue_step(nt_dec_state* st, const int32_t* d_forced, float* d_logit
     }
 
     // Tied output projection.  Its epilogue reduces each row to per-tile (max, sum exp,
-    // best) records.  Greedy needs nothing else, so its logits never reach HBM.  Beam
-    // ranks each row's tiles by their best entries, forms the logits of the first 2K
-    // tiles again (the same kernel and k-order, so the same bits), and selects from
-    // those: its logits never reach HBM either.  Teacher forcing, greedy copy-out and
-    // the plain beam path (nt_set_beam_fused(0)) store the fp32 logits and scan them.
+    // best) records.  Greedy needs nothing else, so its logits never reach HBM unless the
+    // caller asks for them: the projection then writes them to the caller's buffer itself
+    // (96 rows of 32000, forced: 37 us for logits, copy and scan, 24 us for logits with
+    // records and their merge).  Beam ranks each row's tiles by their best entries, forms
+    // the logits of the first 2K tiles again (the same kernel and k-order, so the same
+    // bits), and selects from those: its logits never reach HBM either.  Teacher forcing
+    // without a logits buffer and the plain beam path (nt_set_beam_fused(0)) store the fp32
+    // logits and scan them.
     // An ensemble member writes its logits and folds them into the combined scores.
     if (M > 1) {
       nt::GemmEpi e{};
@@ -946,18 +949,25 @@ nt_status enqueue_step(nt_dec_state* st, const int32_t* d_forced, float* d_logit
       NT_HIP(timed(NT_K_SELECT, s, (double)R * m.V * 4 * (mi == 0 ? 2 : 3), 5.0 * R * m.V, [&] {
         return nt::ens_combine(st->at<float>(p.logits), st->at<float>(p.comb), ctl, K, Rp, m.V, mi, M, top.rule, s);
       }));
-    } else if (K == 1 && !d_logits && !d_forced) {
+    } else if (K == 1 && (d_logits || !d_forced)) {
       const int n_tiles = (m.V + 127) / 128;
       nt::GemmEpi e{};
       e.mode = nt::EPI_TOPK;
       e.part = st->at<float>(p.logits);
       e.k2 = 1;
       e.n_tiles = n_tiles;
+      if (d_logits) {
+        e.out = d_logits;
+        e.ldc = m.V;
+        e.out_f32 = 1;
+        e.out_map = 1;
+        e.sent_list = list;
+      }
       NT_HIP(gemm_dec(NT_K_GEMM_VOCAB, at(p.du), d, m.E, m.V, d, e));
       const float* part = st->at<float>(p.logits);
       const double pbytes = (double)R * n_tiles * nt::topk_record(1) * 4;
-      NT_HIP(timed(NT_K_SELECT, s, pbytes, 0.0, [&] { return nt::greedy_step_fused(part, n_tiles, ss, s); }));
-    } else if (!p.beam_pairs) {   // stored logits: teacher forcing, greedy copy-out, plain beam
+      NT_HIP(timed(NT_K_SELECT, s, pbytes, 0.0, [&] { return nt::greedy_step_fused(part, n_tiles, d_logits, d_forced, ss, s); }));
+    } else if (!p.beam_pairs) {   // stored logits: teacher forcing, plain beam
       nt::GemmEpi e{};
       e.mode = nt::EPI_STORE;
       e.out = at(p.logits);

@@ -225,7 +225,8 @@ __global__ __launch_bounds__(SEL_THREADS) void ens_combine_kernel(const float* _
 // Greedy selection from the projection's per-tile partials [rows][n_tiles][4]
 // (max, sum exp, best value, best index): merged in tile order, then the update.
 __global__ __launch_bounds__(SEL_THREADS) void greedy_fused_kernel(const float* __restrict__ part, int n_tiles,
-                                                                   SearchState st) {
+                                                                   const float* __restrict__ logits,
+                                                                   const int* __restrict__ forced, SearchState st) {
   __shared__ float sm[SEL_THREADS / kWave], ss[SEL_THREADS / kWave], sb[SEL_THREADS / kWave];
   __shared__ int si[SEL_THREADS / kWave];
   asm volatile("" ::"s"(part), "s"(n_tiles), "s"(st.sent_list), "s"(st.ctl));   // one wait for the arguments
@@ -238,6 +239,15 @@ __global__ __launch_bounds__(SEL_THREADS) void greedy_fused_kernel(const float* 
   const int b = st.sent_list[r], nlive = st.ctl[CTL_NLIVE], t = st.ctl[CTL_T];
   asm volatile("" ::"v"(q0.x), "v"(q0.y), "v"(q0.z), "v"(q0.w), "v"(b), "s"(nlive), "s"(t));
   if (r >= nlive) return;
+  // a forced token and its logit, on their way during the reductions
+  const float* x = logits ? logits + (size_t)b * st.V : nullptr;
+  int ftok = -1;
+  float fx = 0.f;
+  if (forced && tid == 0) {
+    ftok = forced[b];
+    if (ftok < 0 || ftok >= st.V) ftok = st.eos;   // out of range: end the sentence
+    fx = x[ftok];
+  }
   if (tid >= n_tiles) q0 = float4{-INFINITY, 0.f, -INFINITY, __int_as_float(INT_MAX)};   // merges as nothing
   MaxSum acc{-INFINITY, 0.f};
   float bv = -INFINITY;
@@ -263,7 +273,8 @@ __global__ __launch_bounds__(SEL_THREADS) void greedy_fused_kernel(const float* 
   const float lse = tot.m + logf(tot.s);
   int tok = fi;
   float lp = fb - lse;
-  if (tok < 0 || tok >= st.V) { tok = st.eos; lp = 0.f; }   // an all-NaN row: end the sentence
+  if (tok < 0 || tok >= st.V) { tok = st.eos; lp = x ? x[tok] - lse : 0.f; }   // an all-NaN row: end the sentence
+  if (forced) { tok = ftok; lp = fx - lse; }
   greedy_update(st, b, tok, lp, t);
 }
 
@@ -1134,10 +1145,12 @@ hipError_t ens_combine(const float* logits, float* comb, const int* ctl, int bea
   return hipGetLastError();
 }
 
-hipError_t greedy_step_fused(const float* part, int n_tiles, const SearchState& st, hipStream_t s) {
+hipError_t greedy_step_fused(const float* part, int n_tiles, const float* logits, const int* forced,
+                             const SearchState& st, hipStream_t s) {
   const int rows = st.B * st.beam;
   if (rows <= 0) return hipSuccess;
-  NT_LAUNCH(greedy_fused_kernel, dim3(rows), dim3(SEL_THREADS), 0, s, part, n_tiles, st);
+  if (forced && !logits) return hipErrorInvalidValue;
+  NT_LAUNCH(greedy_fused_kernel, dim3(rows), dim3(SEL_THREADS), 0, s, part, n_tiles, logits, forced, st);
   return hipGetLastError();
 }
 
