@@ -723,7 +723,11 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    8.5, 1300x32000x512 78 / 52).
 //  * Up to 512 tiles of 64x32, two a CU, those (32): 552x3072x1024 with a folded LayerNorm, 864
 //    tiles, takes 16.1 against 11.5 on 64x128, 300x3072x1024 (480) 9.2 against 11.0,
-//    800x1024x4096 (416) 20.5 against 23.2, 1114x1024x1024 (576) 10.5 against 8.8.
+//    800x1024x4096 (416) 20.5 against 23.2, 1114x1024x1024 (576) 10.5 against 8.8.  Up to 1200
+//    where the device holds the live count: M is then the batch's first step, and with the few
+//    rows of most later steps a 64x128 tile takes 11 to 12 us where this one takes 7 to 8.  The
+//    30-6-1024 model, beam 4, whole jobs with the line at 512 / 1200 / 2400: 100 sentences
+//    95.2 / 90.1 / 90.3 ms, 512 sentences 180.6 / 179.8 / 184.1; base sizes the same.
 //  * Then 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
 //    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
 //    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
@@ -741,7 +745,7 @@ static int phased_tile(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, 
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
   if (m * lda * dt_bytes(dt) >= lim || n * K * dt_bytes(dt) >= lim) return 0;
   const auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  if (role != 2 && !epi.wscale && tiles(64, 32) <= 512) return 32;
+  if (role != 2 && !epi.wscale && tiles(64, 32) <= (epi.ctl ? 1200 : 512)) return 32;
   if (dt == DT::F32) return role == 0 ? 64 : 0;
   if (K % 128 != 0) return 0;
   if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;

@@ -91,14 +91,15 @@ def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
-def test_batch_size_does_not_change_a_translation(dtype):
-    """640 rows a step (phased tiles: cross keys/values, QKV with the cache scatter, FFN,
-    the selection records) against batches of eight sentences (the small tiles)."""
+@pytest.mark.parametrize("n", [160, 420])
+def test_batch_size_does_not_change_a_translation(dtype, n):
+    """640 and 1680 rows a step (phased tiles: cross keys/values, QKV with the cache scatter,
+    FFN, the selection records; at 640 the 64x32 ones past two a CU, at 1680 the larger) against batches of eight sentences (the small tiles)."""
     from paper_2109_08008_amd import nt
     shape = synth.ModelShape(512, 8, 2048, 2, 2, 1100)
     blob = synth.make_weights(shape, seed=5, lively=True)
     rng = np.random.default_rng(6)
-    lens = rng.integers(20, 31, size=160)
+    lens = rng.integers(20, 31, size=n)
     offs = np.concatenate(([0], np.cumsum(lens))).astype(np.int64)
     ids = rng.integers(4, shape.vocab, size=int(offs[-1])).astype(np.int32)
     model = nt.Model(shape, blob, dtype)
