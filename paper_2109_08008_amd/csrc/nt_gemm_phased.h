@@ -1073,7 +1073,9 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   }
   EpiAhead<FN> ahead{};
   ahead.on = epi_whole<T, false, LNF>(epi, n0, BN, N);
-  if (ahead.on) epi_ahead<T, FN, ROLE, LNF>(ahead, epi, M, m0 + wave * 16, n0, fr, fc);
+  // (64x64 tiles have a second workgroup's k-loop to cover the epilogue's loads: 4096x512x512 in
+  // fp32 takes 21.6 us with them here, 21.3 behind the loop)
+  if (FN == 2 && ahead.on) epi_ahead<T, FN, ROLE, LNF>(ahead, epi, M, m0 + wave * 16, n0, fr, fc);
 #pragma unroll
   for (int kt = 2; kt < NS; ++kt) fill(kt);
   floatx4 acc[1][FN];
@@ -1115,6 +1117,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
     if (++kt >= nk) break;
   }
   mfma_drain();
+  if (FN != 2 && ahead.on) epi_ahead<T, FN, ROLE, LNF>(ahead, epi, M, m0 + wave * 16, n0, fr, fc);
   float mu[1] = {0.f}, rs[1] = {1.f};
   if constexpr (LNF) {   // every lane of a row ends with its sums
     const float inv_k = 1.0f / (float)K;
