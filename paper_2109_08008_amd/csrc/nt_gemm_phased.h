@@ -110,8 +110,12 @@ __device__ __forceinline__ void lds_frags8(u32x4 (&f)[4], unsigned p) {
 // ---- one phase: FMH x FNH blocks, both halves of the k-step; next-phase reads; refill ----
 // Operands: c<i><j> accumulators, a<i><k> and b<j><k> fragments; n* the next fragments, from
 // lane addresses p0 / p1 (the k-halves) at offsets o0..; vo*, sb the refill's lane offsets and
-// base, m its LDS address.  A block's accumulator is next touched four MFMAs later at the
-// earliest (past the nops behind the loop for the epilogue), so no wait states are due inside.
+// base, m its LDS address.  The compiler does not look into an asm block for the wait states that
+// gfx9 leaves to software, so the block keeps them: an MFMA stands between each write of M0 and
+// the load that takes its LDS address from it (one is due).  An accumulator comes back two
+// (1 x 2 blocks) to eight MFMAs later, always as the same registers of the same kind of MFMA,
+// which are forwarded (none is due), and nothing else touches it before the nops behind the loop.
+// tests/test_device_waits.py holds the built code to all of them, across the blocks' edges too.
 #define NT_MM(c, b, a) "v_mfma_f32_16x16x32_" NT_MFMA_T " %[" c "], %[" b "], %[" a "], %[" c "]\n\t"
 #define NT_DS(n, p, o) "ds_read_b128 %[" n "], %[" p "] offset:%[" o "]\n\t"
 #define NT_M0 "s_mov_b32 m0, %[m]\n\t"
@@ -131,7 +135,7 @@ __device__ __forceinline__ void lds_frags8(u32x4 (&f)[4], unsigned p) {
   r0 r1 NT_MM("c00", "b0" K, "a0" K) r2 r3 NT_MM("c01", "b1" K, "a0" K)                             \
   r4 r5 NT_MM("c02", "b2" K, "a0" K) r6 r7 NT_MM("c03", "b3" K, "a0" K)
 #define NT_H12(K, r0, r1, r2, r3, r4, r5, r6, r7)                                                   \
-  r0 r1 r2 r3 NT_MM("c00", "b0" K, "a0" K) r4 r5 r6 r7 NT_MM("c01", "b1" K, "a0" K)
+  r0 r1 NT_MM("c00", "b0" K, "a0" K) r2 r3 NT_MM("c01", "b1" K, "a0" K) r4 r5 r6 r7
 #define NT_READS2(H) H("0", NT_DS("n0", "p0", "o0"), NT_DS("n1", "p1", "o0"), "", "", "", "", "", "")
 #define NT_READS4(H)                                                                                \
   H("0", NT_DS("n0", "p0", "o0"), NT_DS("n1", "p0", "o1"), NT_DS("n2", "p1", "o0"),                 \
