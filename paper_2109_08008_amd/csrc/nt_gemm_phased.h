@@ -228,8 +228,16 @@ __device__ __forceinline__ void dma16(const char* src, unsigned char* dst) {
 __device__ __forceinline__ unsigned uniform(unsigned v) { return __builtin_amdgcn_readfirstlane(v); }
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory"); }
-// The MFMAs of an asm block may still be writing their results when it ends.
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+// The MFMAs of an asm block may still be writing their results when it ends.  The compiler does
+// not know, so no use of c may come before the nops: to it, c is written again behind them.
+template <int FM, int FN>
+__device__ __forceinline__ void mfma_drain(floatx4 (&c)[FM][FN]) {
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(c[i][j]));
+}
 
 // The first element of a word.
 template <typename T>
@@ -844,7 +852,7 @@ __global__ __launch_bounds__(W::WGM * W::WGN * kWave, 2) void gemm_phased_kernel
   asm volatile("" : "+v"(lane));
   fr = lane & 15;
   fc = lane >> 4;
-  mfma_drain();
+  mfma_drain(acc);
   wait_vm<0>();                   // the refills past the end have landed
   __builtin_amdgcn_s_barrier();   // in every wave: LDS is free
 
@@ -1120,7 +1128,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
     kstep(kt, a1, b1, a0, b0);
     if (++kt >= nk) break;
   }
-  mfma_drain();
+  mfma_drain(acc);
   if (FN != 2 && ahead.on) epi_ahead<T, FN, ROLE, LNF>(ahead, epi, M, m0 + wave * 16, n0, fr, fc);
   float mu[1] = {0.f}, rs[1] = {1.f};
   if constexpr (LNF) {   // every lane of a row ends with its sums
