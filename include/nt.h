@@ -325,6 +325,13 @@ nt_status nt_op_gemm_ln(int32_t dtype, const void* d_A, int32_t lda, const void*
                         int32_t K, const float* d_colsum, float ln_eps, const float* d_bias, void* d_out,
                         int32_t ldc, int32_t relu, int32_t tile, const float* d_bscale, void* stream);
 
+/* Which tiles nt_op_gemm (ln == 0) or nt_op_gemm_ln (ln != 0) with tile = 0 forms such a
+ * product on: 32 (64x32), 64 (64x128; fp32 64x64), 128 (128x128) or 256 (256x256) for the
+ * tiles whose k-loop runs in phases, 0 for one of the tiles 1..4.  f8 != 0: with d_bscale.
+ * -1 for sizes and types that nt_op_gemm refuses.  Needs no device; for tests that mean to
+ * reach a certain tile. */
+int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8);
+
 /* The FP8 weight quantization nt_load_weights applies with fp8_weights, on the host: W
  * [in][out] fp32 (row-major, y = x W) -> q [out][in] E4M3 codes (OCP, bias 7, ties to
  * even, saturating at 448) and scale [out] fp32, with scale[n] = max_k |W[k][n]| / 448

@@ -740,7 +740,7 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    LayerNorm 5.2 / 4.5), and encoder products beyond on 64x64 (4096x512x512 26.5 / 24.1,
 //    16384x1024x256 93.8 / 80.1): an fp32 k-step is bound by its MFMAs, so what counts is that
 //    the reads and loads stay behind them.
-static int phased_tile(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
+int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
   constexpr unsigned long long lim = 1ull << 32;
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
   if (m * lda * dt_bytes(dt) >= lim || n * K * dt_bytes(dt) >= lim) return 0;
@@ -763,7 +763,7 @@ hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int
   // operand rows move in 16-byte pieces, and the kernel reads A's base as a stand-in
   if (((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Bt)) & 15) != 0) return hipErrorInvalidValue;
   if (M > 0 && N > 0 && tile == 0) {
-    const int bm = phased_tile(dt, lda, M, N, K, epi, role);
+    const int bm = gemm_rows(dt, lda, M, N, K, epi, role);
     if (bm) return dt == DT::F16    ? gemm_phased_f16(A, lda, Bt, M, N, K, epi, s, role, bm)
                    : dt == DT::BF16 ? gemm_phased_bf16(A, lda, Bt, M, N, K, epi, s, role, bm)
                                     : gemm_slim_f32(A, lda, Bt, M, N, K, epi, s, role, bm);

@@ -115,6 +115,10 @@ struct GemmEpi {
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
                 hipStream_t s, int role = 0, int tile = 0);
 
+// What gemm() with tile 0 runs a product on: 32, 64, 128 or 256 for a phased tile (below), 0 for
+// the tiles listed above.  Host only; of epi it reads ctl, wscale and lnf_colsum.
+int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role);
+
 // The same product on the phased tiles (nt_gemm_phased.h), bm = 32: 64x32 output
 // tiles; 64: 64x128; 128 and 256: bm x bm.  gemm() picks them by shape.
 hipError_t gemm_phased_f16(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,

@@ -1886,6 +1886,16 @@ nt_status nt_op_gemm_ln(int32_t dtype, const void* d_A, int32_t lda, const void*
   return NT_OK;
 }
 
+int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8) {
+  if (dtype < NT_F32 || dtype > NT_BF16 || (f8 && dtype != NT_F16)) return -1;
+  if (M < 0 || N <= 0 || K <= 0 || K % 64 != 0 || lda < K) return -1;
+  const float used = 0.f;   // only whether a pointer is set counts
+  nt::GemmEpi e{};
+  if (f8) e.wscale = &used;
+  if (ln) e.lnf_colsum = &used;
+  return nt::gemm_rows(static_cast<DT>(dtype), lda, M, N, K, e, ln ? 1 : 0);
+}
+
 nt_status nt_quantize_fp8(const float* h_W, int32_t in, int32_t out, uint8_t* h_q, float* h_scale) {
   g_err.clear();
   if (!h_W || !h_q || !h_scale) return fail(NT_E_INVALID, "null argument to nt_quantize_fp8");

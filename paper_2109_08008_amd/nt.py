@@ -29,7 +29,7 @@ EXPORTS = [
     "nt_weights_size", "nt_load_weights", "nt_free_model", "nt_workspace_size", "nt_translate_workspace_size",
     "nt_encode", "nt_decode_step", "nt_dec_state_read", "nt_dec_state_info", "nt_dec_state_encoder_out",
     "nt_free_state", "nt_translate", "nt_last_error", "nt_prof_enable", "nt_prof_reset", "nt_prof_get",
-    "nt_op_gemm", "nt_op_gemm_ln", "nt_prof_config", "nt_set_graphs", "nt_set_beam_fused", "nt_set_streams", "nt_prof_units", "nt_op_select",
+    "nt_op_gemm", "nt_op_gemm_ln", "nt_op_gemm_rows", "nt_prof_config", "nt_set_graphs", "nt_set_beam_fused", "nt_set_streams", "nt_prof_units", "nt_op_select",
     "nt_op_select_tiled", "nt_op_select_tiled_noalloc",
     "nt_ensemble", "nt_quantize_fp8",
 ]
@@ -108,6 +108,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                  c_int32, P, P]),
         "nt_op_gemm_ln": (c_int32, [c_int32, P, c_int32, P, c_int32, c_int32, c_int32, P, c_float, P, P, c_int32,
                                     c_int32, c_int32, P, P]),
+        "nt_op_gemm_rows": (c_int32, [c_int32] * 7),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)
@@ -274,6 +275,10 @@ def nt_op_gemm_ln(dtype: str, d_A: int, lda: int, d_Bt: int, M: int, N: int, K: 
                                         c_void_p(d_colsum), float(ln_eps),
                                         c_void_p(d_bias) if d_bias else None, c_void_p(d_out), ldc, int(relu),
                                         tile, c_void_p(d_bscale) if d_bscale else None, _stream(stream)))
+
+
+def nt_op_gemm_rows(dtype: str, M: int, N: int, K: int, ln: bool = False, f8: bool = False, lda: int = 0) -> int:
+    return load_library().nt_op_gemm_rows(DTYPES[dtype], lda or K, M, N, K, int(ln), int(f8))
 
 
 def nt_quantize_fp8(w: np.ndarray):

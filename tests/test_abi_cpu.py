@@ -197,3 +197,25 @@ def test_library_e4m3_rounding_over_the_whole_range(nt):
     decoded = torch.from_numpy(q).view(torch.float8_e4m3fn).to(torch.float64).numpy()
     want = torch.from_numpy(w.T.copy()).to(torch.float8_e4m3fn).to(torch.float64).numpy()
     np.testing.assert_array_equal(decoded, want)
+
+
+def test_tiled_gemm_cases_reach_their_tiles(nt):
+    """The sizes at which the GPU tests compare the tiles are still formed on them."""
+    from tests import test_gpu_gemm_phased as t
+    seen = {d: set() for d in t.TILES}
+    for cases, ln in ((t.PROJ, False), (t.FOLDED, True)):
+        for c in cases:
+            for d, want in zip(t.TILES, c[3:]):
+                for dt in ("f16", "bf16") if d == "16-bit" else ("f16",) if d == "f8" else ("f32",):
+                    assert nt.nt_op_gemm_rows(dt, *c[:3], ln=ln, f8=d == "f8") == want, (c, dt, ln)
+                seen[d].add((ln, want))
+    assert seen == {"16-bit": {(False, 0), (False, 32), (False, 64), (False, 128), (False, 256), (True, 32), (True, 64),
+                               (True, 128)},
+                    "f8": {(False, 0), (False, 128), (True, 0), (True, 128)},
+                    "f32": {(False, 32), (False, 64), (True, 0), (True, 32)}}
+    # refused sizes and types; operands past 32-bit offsets
+    for args, kw in ((("f16", 8, 8, 96), {}), (("f32", 8, 8, 64), {"f8": True}), (("f16", 8, 0, 64), {}),
+                     (("f16", 8, 8, 128), {"lda": 64})):
+        assert nt.nt_op_gemm_rows(*args, **kw) == -1
+    assert nt.nt_op_gemm_rows("f16", 1 << 20, 1024, 2048) == 0
+    assert nt.nt_op_gemm_rows("f16", 1 << 20, 1024, 1024) == 256

@@ -37,22 +37,50 @@ def _inputs(dtype, M, N, K, seed):
     return a, w, scale, r(N), r(M, N).to(tdt)
 
 
+# sizes and what tile 0 runs them on, by kind of weight: 32 is the 64x32 phased tile, 64 the 64x128
+# (fp32: 64x64), 128 and 256 the square ones, 0 a tile of nt_gemm.hip
+TILES = ("16-bit", "f8", "f32")
+PROJ = [
+    (1, 8, 64, 32, 0, 32),              # one row, one k-step
+    (65, 100, 192, 32, 0, 32),          # two rows of tiles, an odd number of k-steps, ragged N
+    (128, 2050, 2048, 32, 0, 32),       # more k-steps than LDS holds, two columns in the last tile
+    (450, 2048, 128, 32, 128, 32),      # 512 tiles of 64x32, the last row of two rows
+    (897, 1024, 384, 32, 128, 32),      # one row in the last tile
+    (577, 2048, 128, 64, 128, 64),      # 64x128: one row in the last tile, the shortest k-loop
+    (1089, 1024, 384, 64, 128, 64),     # three pairs of k-steps
+    (1090, 1024, 2048, 64, 128, 64),    # a long k-loop
+    (641, 2051, 256, 64, 128, 64),      # rows of 2051 elements: no vector access
+    (1100, 1000, 512, 64, 128, 64),     # N ending inside a tile
+    (1089, 1024, 192, 0, 0, 64),        # an odd number of k-steps
+    (4095, 1000, 512, 128, 128, 64),    # 128x128, N ending inside a tile
+    (4225, 1031, 256, 128, 128, 64),    # 128x128, rows of 1031 elements: no vector access
+    (4097, 4096, 256, 128, 128, 64),    # 128x128 where 256x256 would leave a round nearly empty
+    (4096, 4096, 128, 256, 128, 64),    # 256x256, whole tiles
+    (4081, 4092, 640, 256, 128, 64),    # 256x256, ragged in both directions
+]
+FOLDED = [
+    (3, 40, 64, 32, 0, 32),
+    (65, 1000, 448, 32, 0, 32),
+    (513, 1024, 128, 32, 0, 32),
+    (449, 2048, 512, 32, 128, 32),
+    (577, 2048, 512, 64, 128, 0),       # 64x128: one row in the last tile, whole columns
+    (1089, 1024, 128, 64, 128, 0),      # the shortest k-loop
+    (1025, 1030, 384, 64, 128, 0),      # rows of 1030 elements: no vector access
+    (2111, 3072, 256, 128, 128, 0),     # 128x128
+]
+
+
+def _rows(dtype, case):
+    return case[3 + TILES.index(dtype if dtype in TILES else "16-bit")]
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
-@pytest.mark.parametrize("M,N,K", [
-    (1, 8, 64),            # 64x32 tiles: one row, one k-step
-    (65, 100, 192),        # 64x32: two rows of tiles, an odd number of k-steps, ragged N
-    (128, 2050, 2048),     # 64x32: more k-steps than LDS holds, two columns in the last tile
-    (450, 2048, 128),      # 64x128 tiles, the last one of two rows, the shortest k-loop
-    (897, 1024, 384),      # 64x128: one row in the last tile
-    (4095, 1000, 512),     # 128x128, N ending inside a tile
-    (4225, 1031, 256),     # 128x128, rows of 1031 elements: no vector access
-    (4097, 4096, 256),     # 128x128 where 256x256 would leave a round nearly empty
-    (4096, 4096, 128),     # 256x256, whole tiles
-    (4081, 4092, 640),     # 256x256, ragged in both directions
-])
-def test_projection_equals_small_tile(dtype, M, N, K):
+@pytest.mark.parametrize("case", PROJ, ids=str)
+def test_projection_equals_small_tile(dtype, case):
     import torch
     from paper_2109_08008_amd import nt
+    M, N, K = case[:3]
+    assert nt.nt_op_gemm_rows("f16" if dtype == "f8" else dtype, M, N, K, f8=dtype == "f8") == _rows(dtype, case)
     a, w, scale, bias, resid = _inputs(dtype, M, N, K, M + N + K)
     for mode in ("store", "relu", "resid", "f32", "unaligned"):
         got = []
@@ -71,10 +99,12 @@ def test_projection_equals_small_tile(dtype, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
-@pytest.mark.parametrize("M,N,K", [(3, 40, 64), (65, 1000, 448), (513, 1024, 128), (1025, 1030, 384), (2111, 3072, 256), (449, 2048, 512)])
-def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
+@pytest.mark.parametrize("case", FOLDED, ids=str)
+def test_folded_layernorm_equals_small_tile(dtype, case):
     import torch
     from paper_2109_08008_amd import nt
+    M, N, K = case[:3]
+    assert nt.nt_op_gemm_rows("f16" if dtype == "f8" else dtype, M, N, K, ln=True, f8=dtype == "f8") == _rows(dtype, case)
     a, w, scale, bias, _ = _inputs(dtype, M, N, K, M + N + K)
     wf = w.view(torch.float8_e4m3fn).double() * scale.double()[:, None] if dtype == "f8" else w.double()
     colsum = wf.sum(1).float()
@@ -93,8 +123,9 @@ def test_folded_layernorm_equals_small_tile(dtype, M, N, K):
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f8", "f32"])
 @pytest.mark.parametrize("n", [160, 420])
 def test_batch_size_does_not_change_a_translation(dtype, n):
-    """640 and 1680 rows a step (phased tiles: cross keys/values, QKV with the cache scatter,
-    FFN, the selection records; at 640 the 64x32 ones past two a CU, at 1680 the larger) against batches of eight sentences (the small tiles)."""
+    """640 and 1680 rows a step (phased tiles: cross keys/values, QKV with the cache scatter, FFN,
+    the selection records; at 640 the 64x32 ones past two a CU, at 1680 64x128 for QKV and FFN1)
+    against batches of eight sentences (small tiles throughout)."""
     from paper_2109_08008_amd import nt
     shape = synth.ModelShape(512, 8, 2048, 2, 2, 1100)
     blob = synth.make_weights(shape, seed=5, lively=True)
