@@ -300,8 +300,9 @@ nt_status nt_translate(nt_model* m, const nt_search_cfg* search, const int32_t* 
  * ReLU if relu != 0.  A, Bt, resid and out are device arrays in `dtype` (out is fp32
  * if out_f32); rows of A are lda elements apart, rows of out/resid ldc elements apart;
  * Bt is [N][K] contiguous.  K % 64 == 0; rows of A start 16-byte aligned.  tile: 0 = chosen by
- * shape, 1 = 64x32, 2 = 128x128, 3 = 128x64, 4 = 64x128 output tiles (the choice never
- * changes a result).  d_bscale: NULL, or (dtype NT_F16 only) Bt holds FP8 E4M3 bytes and
+ * shape, as the translation path does, among the tiles 1..4 and those of nt_op_gemm_rows;
+ * 1 = 64x32, 2 = 128x128, 3 = 128x64, 4 = 64x128 output tiles (the choice never changes a
+ * result).  d_bscale: NULL, or (dtype NT_F16 only) Bt holds FP8 E4M3 bytes and
  * column n of the product is multiplied by d_bscale[n] (fp32), as for the weights of an
  * fp8_weights model; tiles 1 and 4 are then 32x64 and 64x64.  Asynchronous. */
 nt_status nt_op_gemm(int32_t dtype, const void* d_A, int32_t lda, const void* d_Bt, int32_t M, int32_t N, int32_t K,

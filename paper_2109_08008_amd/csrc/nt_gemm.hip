@@ -2,7 +2,10 @@
 // (the "MM" that dominates the paper's GPU profile, Sec. 4.4) as one MFMA GEMM for
 // gfx950:  C[M,N] = A[M,K] . Bt[N,K]^T with fp32 accumulation and a fused epilogue.
 //
-// Tiling: BMxBN output tile (128x128, 128x64 or 64x32) per 256-thread workgroup, four
+// Most products run on the phased tiles of nt_gemm_phased.h; gemm() at the end chooses.  Here are
+// the tiles for the others, the recomputed selection tiles, and the choice.
+//
+// Tiling: BMxBN output tile (128x128, 64x128, 128x64 or 64x32) per 256-thread workgroup, four
 // waves in a 2x2 grid of 16x16 MFMA blocks.  K advances 128 bytes per step (64 halves or 32
 // floats) through a ring of STAGES LDS slots filled by direct global->LDS loads
 // (global_load_lds_dwordx4), so STAGES-1 k-tiles are in flight while one is multiplied;
@@ -592,9 +595,14 @@ hipError_t launch_tile(const void* A, int lda, const void* Bt, int M, int N, int
   return hipGetLastError();
 }
 
-// Tile choice by problem size, measured on MI355X with four batches' GEMMs in flight at
-// once (how nt_translate runs them).  LDS footprint matters more than pipeline depth, so
-// the big tiles use two stages.
+// Tile choice by problem size among the tiles of this file.  It decides for the products that
+// gemm_rows (below) leaves to them: an odd number of k-steps past the 64x32 phased tile's range,
+// FP8 weights on few tiles or with an odd number of k-steps, fp32 decoder steps past that range,
+// selection records and stored logits in fp32, operands past 32-bit offsets.  (An explicit tile
+// argument reaches all of them at any size.)  Measured on MI355X with four batches' GEMMs in
+// flight at once (how nt_translate runs them), many of the figures at sizes that have since moved
+// to the phased tiles.  LDS footprint matters more than pipeline depth, so the big tiles use two
+// stages.
 //   M >= 4096 (encoder, big batches): 128x64 for N <= 2048, else 128x128; and
 //                      128x128 for the FFN's second GEMM (K >= 2048) from 8M outputs up
 //                      (16384x512x2048: 40.6 us against 52.1; 16384x1024x4096: 135.4
@@ -725,15 +733,20 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    tiles, takes 16.1 against 11.5 on 64x128, 300x3072x1024 (480) 9.2 against 11.0,
 //    800x1024x4096 (416) 20.5 against 23.2, 1114x1024x1024 (576) 10.5 against 8.8.  Up to 1200
 //    where the device holds the live count: M is then the batch's first step, and with the few
-//    rows of most later steps a 64x128 tile takes 11 to 12 us where this one takes 7 to 8.  The
-//    30-6-1024 model, beam 4, whole jobs with the line at 512 / 1200 / 2400: 100 sentences
-//    95.2 / 90.1 / 90.3 ms, 512 sentences 180.6 / 179.8 / 184.1; base sizes the same.
+//    rows of most later steps a 64x128 tile takes 11 to 12 us where this one takes 7 to 8 (tiles
+//    past the live rows still issue two k-steps of loads before they know).  Whole jobs with the
+//    line at 512 / 1200 / 2400, ms, beam 4 where none is given: 30-6-1024, 100 sentences
+//    97.0 / 90.7 / 90.6, 512 182.6 / 180.4 / 185.0; 6-6-512, 100 sentences 47.3 / 47.2 / 47.2,
+//    325 70.4 / 67.0 / 67.0, 600 84.5 / 83.1 / 86.6, 325 in fp32 162.6 / 145.9 / 145.7, 160 in
+//    bf16 at beam 5 61.6 / 58.1 / 58.2; 35-1-512 greedy, 1024 sentences 37.6 / 37.9 / 37.8.
 //  * Then 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
 //    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
 //    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
 //    stays until it needs more rounds of the GPU than 128x128 (2160x3072x1024: 28.7 / 24.5).
-//  * 256x256 where its tiles fill their last round of CUs to 90%: 16384x4096x1024 127 against
-//    142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90 against 82.
+//  * 256x256 where its tiles fill 90% of the rounds of CUs that they take: 16384x4096x1024 127
+//    against 142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90
+//    against 82.  Over many rounds the last one may be nearly empty: 37632x4096x1024 (9.2 rounds)
+//    305 against 328, 41216x4096x1024 (10.1) 340 against 363, 148480x1024x512 (9.1) 242 against 261.
 //  * FP8 weights run on 128x128 from 64 tiles on (this file's / phased: 1300x512x2048, 44 tiles,
 //    14.7 / 20.6; 1114x1024x1024, 72, 15.3 / 12.9).
 //  * fp32 runs on 64x32 up to 512 of them (1000x512x512 9.4 / 8.2, 8x384x128 with a folded

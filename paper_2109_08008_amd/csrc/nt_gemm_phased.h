@@ -291,9 +291,6 @@ __device__ __forceinline__ void mode_switch(int mode, F& f) {
   }
 }
 
-// The epilogue of a wave's FM x FN blocks: lane (fr, fc) holds columns nw + 16 j + 4 fc .. + 3 of
-// the rows mw + 16 i + fr.  mu, rs: the rows' statistics (folded LayerNorm); cs: LDS of the
-// wave's own for half its rows in fp32, ln_mu / ln_rs the statistics of all its rows in LDS.
 // A word that no block of this launch writes, through the scalar cache.
 __device__ __forceinline__ int scalar_int(const int* p) {
   return *reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(p));
@@ -347,6 +344,9 @@ __device__ __forceinline__ bool epi_whole(const GemmEpi& epi, int nw, int cols, 
   return nw + cols <= N && (al & 15) == 0;
 }
 
+// The epilogue of a wave's FM x FN blocks: lane (fr, fc) holds columns nw + 16 j + 4 fc .. + 3 of
+// the rows mw + 16 i + fr.  mu, rs: the rows' statistics (folded LayerNorm); cs: LDS of the
+// wave's own for half its rows in fp32, ln_mu / ln_rs the statistics of all its rows in LDS.
 template <typename T, int FM, int FN, int ROLE, bool F8, bool LNF>
 __device__ __forceinline__ void phased_epilogue(floatx4 (&c)[FM][FN], const GemmEpi& epi, int M, int N, int mw, int nw,
                                                 int t_slot, int fr, int fc, const float (&mu)[FM],

@@ -108,8 +108,9 @@ struct GemmEpi {
   int pair_k = 1;
 };
 
-// role: 0 encoder, 1 decoder step, 2 output projection.  Only the kernel's symbol name
-// depends on it, so profiles separate the three uses.  (Role 3 is gemm_pairs below.)
+// role: 0 encoder, 1 decoder step, 2 output projection.  The kernel's symbol name carries it, so
+// profiles separate the three uses, and the tile rules look at it (a result does not depend on
+// it).  (Role 3 is gemm_pairs below.)
 // tile: 0 = chosen by shape (among the phased tiles too), 1 = 64x32, 2 = 128x128, 3 = 128x64,
 // 4 = 64x128 (never changes a result).
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,
