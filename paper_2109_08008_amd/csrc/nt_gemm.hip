@@ -747,8 +747,16 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    against 142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90
 //    against 82.  Over many rounds the last one may be nearly empty: 37632x4096x1024 (9.2 rounds)
 //    305 against 328, 41216x4096x1024 (10.1) 340 against 363, 148480x1024x512 (9.1) 242 against 261.
-//  * FP8 weights run on 128x128 from 64 tiles on (this file's / phased: 1300x512x2048, 44 tiles,
-//    14.7 / 20.6; 1114x1024x1024, 72, 15.3 / 12.9).
+//  * FP8 weights run on 128x128 from 144 tiles on, where this file's tiles stop being faster (this
+//    file's / phased: 1000x1024x256, 64 tiles, 5.0 / 6.6; 1300x1536x512, 132, 7.9 / 8.8;
+//    1000x2304x768, 144, 11.7 / 10.7; 2160x1536x512, 204, 14.6 / 9.2).  With a folded LayerNorm
+//    (500x2048x512, 64, 7.4 / 11.3; 1300x1536x512, 132, 11.5 / 11.5; 1700x1536x512, 168, 14.4 /
+//    11.7) also where this file's 64x128 tiles, two a CU, need as many rounds of the GPU as
+//    128x128, one a CU: 1300x3072x1024 (504 and 264 tiles) 23.1 / 25.2, 2160x2048x512 (544, 272)
+//    19.4 / 16.6.  A decoder step's other products, which have only 64x128 to go back to, from 64
+//    on.  Whole jobs of the 6-6-512 model, beam 4, with both lines at 64 / as they are: 100
+//    sentences 60.0 / 56.2 ms, 325 85.0 / 77.9; with all three at 144, 30-6-1024, 270 sentences
+//    of 30 words 77.5 against 71.7.
 //  * fp32 runs on 64x32 up to 512 of them (1000x512x512 9.4 / 8.2, 8x384x128 with a folded
 //    LayerNorm 5.2 / 4.5), and encoder products beyond on 64x64 (4096x512x512 26.5 / 24.1,
 //    16384x1024x256 93.8 / 80.1): an fp32 k-step is bound by its MFMAs, so what counts is that
@@ -763,7 +771,10 @@ int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role)
   if (K % 128 != 0) return 0;
   if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
   const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
-  if (epi.wscale) return t128 >= 64 ? 128 : 0;
+  if (epi.wscale) {
+    if (epi.lnf_colsum && (t128 + 255) / 256 > (t64 + 511) / 512) return 0;
+    return t128 >= (role == 1 && !epi.lnf_colsum ? 64 : 144) ? 128 : 0;
+  }
   if (epi.lnf_colsum) return (t128 + 511) / 512 < (t64 + 767) / 768 ? 128 : 64;
   if (t64 <= 256) return 64;
   const long long rounds = (t256 + 255) / 256;

@@ -44,14 +44,16 @@ PROJ = [
     (1, 8, 64, 32, 0, 32),              # one row, one k-step
     (65, 100, 192, 32, 0, 32),          # two rows of tiles, an odd number of k-steps, ragged N
     (128, 2050, 2048, 32, 0, 32),       # more k-steps than LDS holds, two columns in the last tile
-    (450, 2048, 128, 32, 128, 32),      # 512 tiles of 64x32, the last row of two rows
-    (897, 1024, 384, 32, 128, 32),      # one row in the last tile
-    (577, 2048, 128, 64, 128, 64),      # 64x128: one row in the last tile, the shortest k-loop
-    (1089, 1024, 384, 64, 128, 64),     # three pairs of k-steps
-    (1090, 1024, 2048, 64, 128, 64),    # a long k-loop
-    (641, 2051, 256, 64, 128, 64),      # rows of 2051 elements: no vector access
-    (1100, 1000, 512, 64, 128, 64),     # N ending inside a tile
+    (450, 2048, 128, 32, 0, 32),        # 512 tiles of 64x32, the last row of two rows
+    (897, 1024, 384, 32, 0, 32),        # one row in the last tile
+    (577, 2048, 128, 64, 0, 64),        # 64x128: one row in the last tile, the shortest k-loop
+    (1089, 1024, 384, 64, 0, 64),       # three pairs of k-steps
+    (1090, 1024, 2048, 64, 0, 64),      # a long k-loop
+    (641, 2051, 256, 64, 0, 64),        # rows of 2051 elements: no vector access
+    (1100, 1000, 512, 64, 0, 64),       # N ending inside a tile
     (1089, 1024, 192, 0, 0, 64),        # an odd number of k-steps
+    (2176, 1024, 384, 128, 0, 64),      # FP8: the last size on the older tiles
+    (2177, 1024, 384, 128, 128, 64),    # one row in the last tile
     (4095, 1000, 512, 128, 128, 64),    # 128x128, N ending inside a tile
     (4225, 1031, 256, 128, 128, 64),    # 128x128, rows of 1031 elements: no vector access
     (4097, 4096, 256, 128, 128, 64),    # 128x128 where 256x256 would leave a round nearly empty
@@ -62,10 +64,13 @@ FOLDED = [
     (3, 40, 64, 32, 0, 32),
     (65, 1000, 448, 32, 0, 32),
     (513, 1024, 128, 32, 0, 32),
-    (449, 2048, 512, 32, 128, 32),
-    (577, 2048, 512, 64, 128, 0),       # 64x128: one row in the last tile, whole columns
-    (1089, 1024, 128, 64, 128, 0),      # the shortest k-loop
-    (1025, 1030, 384, 64, 128, 0),      # rows of 1030 elements: no vector access
+    (449, 2048, 512, 32, 0, 32),
+    (577, 2048, 512, 64, 0, 0),         # 64x128: one row in the last tile, whole columns
+    (1089, 1024, 128, 64, 0, 0),        # the shortest k-loop
+    (1025, 1030, 384, 64, 0, 0),        # rows of 1030 elements: no vector access
+    (2177, 1030, 256, 64, 128, 0),      # the same for FP8
+    (1300, 3072, 128, 64, 0, 0),        # FP8: 264 tiles of 128x128, 504 of 64x128
+    (2177, 1024, 256, 64, 128, 0),      # FP8: one row in the last tile
     (2111, 3072, 256, 128, 128, 0),     # 128x128
 ]
 
