@@ -1016,17 +1016,20 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
   asm volatile("" ::"s"(epi.ctl), "s"(epi.bias), "s"(epi.out), "s"(epi.ldc), "s"(epi.mode), "s"(epi.resid),
                "s"(epi.lnf_colsum), "s"(epi.sent_list), "s"(epi.beam), "s"(epi.ctl_rows), "s"(A), "s"(lda), "s"(K),
                "s"(N), "s"(M), "s"(Bt), "s"(tiles_n));
-  // A decoder step's tiles do not depend on how many rows are live (the grid's y is the tile row,
-  // an XCD owns a panel of columns), so their first loads are under way before the count is
-  // known; rows past the live ones are rows of the same buffers.
+  // A decoder step's tiles do not depend on how many rows are live (the grid's y is the tile row),
+  // so their first loads are under way before the count is known; rows past the live ones are rows
+  // of the same buffers.  An XCD owns a panel of columns where they divide evenly among the eight.
+  // Otherwise tiles go round the XCDs as they come: panels of ceil(tiles_n / 8) would leave some
+  // idle (with a folded LayerNorm, times those of nt_gemm.hip's 64x32 tile: 2160x384x128, on six
+  // XCDs, 1.24 with panels and 0.89 without, 3500x128x128, on four, 1.09 and 0.86, 800x1152x384
+  // 1.10 and 0.83).
   int tm, tn, n_live = 0, t_slot = 0;
   if constexpr (ROLE == 1) {
     const int* ctl = epi.ctl ? epi.ctl : reinterpret_cast<const int*>(A);   // (no branch to wait in)
     n_live = scalar_int(ctl + CTL_NLIVE);
     t_slot = scalar_int(ctl + CTL_T);
     tm = blockIdx.y;
-    tn = blockIdx.x % 8 * ((tiles_n + 7) / 8) + blockIdx.x / 8;
-    if (tn >= tiles_n) return;
+    tn = tiles_n % 8 ? blockIdx.x : blockIdx.x % 8 * (tiles_n / 8) + blockIdx.x / 8;
   } else {
     // XCD-contiguous, then grouped by 8 tile-rows
     const int ntiles = tiles_m * tiles_n;
@@ -1150,7 +1153,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const T* __restrict__ A,
 template <typename T, int FN, int NS, int ROLE, bool LNF>
 hipError_t launch_slim(const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi, hipStream_t s) {
   const int tm = (M + 63) / 64, tn = (N + 16 * FN - 1) / (16 * FN);
-  const dim3 grid = ROLE == 1 ? dim3((tn + 7) / 8 * 8, tm) : dim3(tm * tn);
+  const dim3 grid = ROLE == 1 ? dim3(tn, tm) : dim3(tm * tn);
   NT_LAUNCH((gemm_slim_kernel<T, FN, NS, ROLE, LNF>), grid, dim3(256), 0, s, static_cast<const T*>(A), lda, Bt, M, N,
             K, epi, tm, tn);
   return hipGetLastError();

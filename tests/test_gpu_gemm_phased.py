@@ -63,6 +63,9 @@ PROJ = [
 FOLDED = [
     (3, 40, 64, 32, 0, 32),
     (65, 1000, 448, 32, 0, 32),
+    (200, 72, 128, 32, 0, 32),          # columns of tiles that do not divide among the XCDs: three
+    (2600, 384, 128, 32, 0, 32),        # twelve
+    (129, 1152, 192, 32, 0, 32),        # 36
     (513, 1024, 128, 32, 0, 32),
     (449, 2048, 512, 32, 0, 32),
     (577, 2048, 512, 64, 0, 0),         # 64x128: one row in the last tile, whole columns
