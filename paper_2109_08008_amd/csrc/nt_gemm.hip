@@ -739,6 +739,12 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    97.0 / 90.7 / 90.6, 512 182.6 / 180.4 / 185.0; 6-6-512, 100 sentences 47.3 / 47.2 / 47.2,
 //    325 70.4 / 67.0 / 67.0, 600 84.5 / 83.1 / 86.6, 325 in fp32 162.6 / 145.9 / 145.7, 160 in
 //    bf16 at beam 5 61.6 / 58.1 / 58.2; 35-1-512 greedy, 1024 sentences 37.6 / 37.9 / 37.8.
+//    A tile fills six k-steps of LDS whatever K is, and two a CU is all that fits: with four k-steps
+//    or fewer (fp32: two) and more than one tile a CU, this file's 64x32 tile is faster up to those 512
+//    (1300x768x256 4.5 / 4.8, 1000x1024x128 3.9 / 4.3, 65x8000x128 to fp32 3.9 / 4.3, fp32 2160x256x64
+//    4.6 / 5.0; 2160x512x128, 544 tiles, 5.3 / 4.3 on 64x128).  Decoder steps are left out: with a
+//    folded LayerNorm the phased tile wins there too, and the 9-1-256 model, beam 4, 400 sentences,
+//    takes 21.5 ms with it and 21.9 without.
 //  * Then 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
 //    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
 //    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
@@ -766,7 +772,9 @@ int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role)
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
   if (m * lda * dt_bytes(dt) >= lim || n * K * dt_bytes(dt) >= lim) return 0;
   const auto tiles = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  if (role != 2 && !epi.wscale && tiles(64, 32) <= (epi.ctl ? 1200 : 512)) return 32;
+  const long long t32 = tiles(64, 32);
+  if (role != 2 && !epi.wscale && t32 <= (epi.ctl ? 1200 : 512))
+    return role == 0 && t32 > 256 && K <= (dt == DT::F32 ? 64 : 256) ? 0 : 32;
   if (dt == DT::F32) return role == 0 ? 64 : 0;
   if (K % 128 != 0) return 0;
   if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;

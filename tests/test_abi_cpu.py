@@ -212,7 +212,7 @@ def test_tiled_gemm_cases_reach_their_tiles(nt):
     assert seen == {"16-bit": {(False, 0), (False, 32), (False, 64), (False, 128), (False, 256), (True, 32), (True, 64),
                                (True, 128)},
                     "f8": {(False, 0), (False, 128), (True, 0), (True, 128)},
-                    "f32": {(False, 32), (False, 64), (True, 0), (True, 32)}}
+                    "f32": {(False, 0), (False, 32), (False, 64), (True, 0), (True, 32)}}
     # refused sizes and types; operands past 32-bit offsets
     for args, kw in ((("f16", 8, 8, 96), {}), (("f32", 8, 8, 64), {"f8": True}), (("f16", 8, 0, 64), {}),
                      (("f16", 8, 8, 128), {"lda": 64})):

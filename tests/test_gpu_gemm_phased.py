@@ -44,7 +44,11 @@ PROJ = [
     (1, 8, 64, 32, 0, 32),              # one row, one k-step
     (65, 100, 192, 32, 0, 32),          # two rows of tiles, an odd number of k-steps, ragged N
     (128, 2050, 2048, 32, 0, 32),       # more k-steps than LDS holds, two columns in the last tile
-    (450, 2048, 128, 32, 0, 32),        # 512 tiles of 64x32, the last row of two rows
+    (450, 2048, 128, 0, 0, 32),         # 512 tiles of 64x32, the last row of two rows; four k-steps or fewer
+    (450, 2048, 320, 32, 0, 32),        # five k-steps
+    (2049, 250, 256, 0, 0, 32),         # 264 tiles
+    (2048, 250, 256, 32, 0, 32),        # 256 tiles
+    (2049, 250, 64, 0, 0, 0),           # two fp32 k-steps
     (897, 1024, 384, 32, 0, 32),        # one row in the last tile
     (577, 2048, 128, 64, 0, 64),        # 64x128: one row in the last tile, the shortest k-loop
     (1089, 1024, 384, 64, 0, 64),       # three pairs of k-steps
