@@ -757,8 +757,8 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    file's / phased: 1000x1024x256, 64 tiles, 5.0 / 6.6; 1300x1536x512, 132, 7.9 / 8.8;
 //    1000x2304x768, 144, 11.7 / 10.7; 2160x1536x512, 204, 14.6 / 9.2).  With a folded LayerNorm
 //    (500x2048x512, 64, 7.4 / 11.3; 1300x1536x512, 132, 11.5 / 11.5; 1700x1536x512, 168, 14.4 /
-//    11.7) also where this file's 64x128 tiles, two a CU, need as many rounds of the GPU as
-//    128x128, one a CU: 1300x3072x1024 (504 and 264 tiles) 23.1 / 25.2, 2160x2048x512 (544, 272)
+//    11.7) also where this file's 64x128 tiles, counted two a CU, need as many rounds of the GPU
+//    as 128x128 one a CU: 1300x3072x1024 (504 and 264 tiles) 23.1 / 25.2, 2160x2048x512 (544, 272)
 //    19.4 / 16.6.  A decoder step's other products, which have only 64x128 to go back to, from 64
 //    on.  Whole jobs of the 6-6-512 model, beam 4, with both lines at 64 / as they are: 100
 //    sentences 60.0 / 56.2 ms, 325 85.0 / 77.9; with all three at 144, 30-6-1024, 270 sentences

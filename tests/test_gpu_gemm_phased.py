@@ -94,14 +94,17 @@ def test_projection_equals_small_tile(dtype, case):
     M, N, K = case[:3]
     assert nt.nt_op_gemm_rows("f16" if dtype == "f8" else dtype, M, N, K, f8=dtype == "f8") == _rows(dtype, case)
     a, w, scale, bias, resid = _inputs(dtype, M, N, K, M + N + K)
-    for mode in ("store", "relu", "resid", "f32", "unaligned"):
+    for mode in ("store", "relu", "resid", "in place", "f32", "unaligned"):
         got = []
         for tile in (0, 1):
             out = torch.full((M * N + 1,), float("nan"), device="cuda",
                              dtype=torch.float32 if mode == "f32" else a.dtype)
             at = out[1:] if mode == "unaligned" else out[:-1]
+            if mode == "in place":      # the residual is what the output overwrites
+                at.copy_(resid.view(-1))
+            add = at if mode == "in place" else resid if mode == "resid" else None
             nt.nt_op_gemm("f16" if dtype == "f8" else dtype, a.data_ptr(), K, w.data_ptr(), M, N, K, bias.data_ptr(),
-                          resid.data_ptr() if mode == "resid" else None, at.data_ptr(), N, out_f32=mode == "f32",
+                          add.data_ptr() if add is not None else None, at.data_ptr(), N, out_f32=mode == "f32",
                           relu=mode == "relu", tile=tile, d_bscale=scale.data_ptr() if scale is not None else None)
             torch.cuda.synchronize()
             edge = out[0] if mode == "unaligned" else out[-1]
