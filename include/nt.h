@@ -328,10 +328,11 @@ nt_status nt_op_gemm_ln(int32_t dtype, const void* d_A, int32_t lda, const void*
 
 /* Which tiles nt_op_gemm (ln == 0) or nt_op_gemm_ln (ln != 0) with tile = 0 forms such a
  * product on: 32 (64x32), 64 (64x128; fp32 64x64), 128 (128x128) or 256 (256x256) for the
- * tiles whose k-loop runs in phases, 0 for one of the tiles 1..4.  f8 != 0: with d_bscale.
- * -1 for sizes and types that nt_op_gemm refuses.  Needs no device; for tests that mean to
- * reach a certain tile. */
-int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8);
+ * tiles whose k-loop runs in phases, 0 for one of the tiles 1..4.  f8 != 0: with d_bscale;
+ * out_f32 as for nt_op_gemm; ldc = N.  -1 for sizes and types that nt_op_gemm refuses.  Needs
+ * no device; for tests that mean to reach a certain tile. */
+int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8,
+                        int32_t out_f32);
 
 /* The FP8 weight quantization nt_load_weights applies with fp8_weights, on the host: W
  * [in][out] fp32 (row-major, y = x W) -> q [out][in] E4M3 codes (OCP, bias 7, ties to

@@ -746,13 +746,18 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //    folded LayerNorm the phased tile wins there too, and the 9-1-256 model, beam 4, 400 sentences,
 //    takes 21.5 ms with it and 21.9 without.
 //  * Then 64x128 tiles up to one a CU (4096x512x2048, 256 tiles: 15.3 against 18.9 on 128x128),
-//    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  A folded LayerNorm's statistics
+//    128x128 beyond (8192x512x512, 512: 9.3 against 13.8).  Where N ends inside a tile its ragged
+//    columns are the launch's longest, and 64x128 stays up to two a CU unless the k-loop is long
+//    (2600x1000x128, 328 tiles, 6.0 / 7.2, with a residual and K = 1024 13.4 / 15.0; K = 2048
+//    20.6 / 19.8).  A folded LayerNorm's statistics
 //    take longest where a CU has one workgroup, so there 64x128, three of which share a CU,
 //    stays until it needs more rounds of the GPU than 128x128 (2160x3072x1024: 28.7 / 24.5).
 //  * 256x256 where its tiles fill 90% of the rounds of CUs that they take: 16384x4096x1024 127
 //    against 142 on 128x128, 8192x2048x512 21.9 against 23.8; 12000x3072x1024 (2.2 rounds) 90
 //    against 82.  Over many rounds the last one may be nearly empty: 37632x4096x1024 (9.2 rounds)
 //    305 against 328, 41216x4096x1024 (10.1) 340 against 363, 148480x1024x512 (9.1) 242 against 261.
+//    Rows that no vector store takes keep a short product on 128x128, where a second workgroup works
+//    meanwhile: 2600x32001 to fp32, K = 128 154 against 137, 256 167 against 152, 768 231 against 253.
 //  * FP8 weights run on 128x128 from 144 tiles on, where this file's tiles stop being faster (this
 //    file's / phased: 1000x1024x256, 64 tiles, 5.0 / 6.6; 1300x1536x512, 132, 7.9 / 8.8;
 //    1000x2304x768, 144, 11.7 / 10.7; 2160x1536x512, 204, 14.6 / 9.2).  With a folded LayerNorm
@@ -766,7 +771,8 @@ hipError_t gemm_pairs(DT dt, const void* A, int lda, const void* Bt, int N, int 
 //  * fp32 runs on 64x32 up to 512 of them (1000x512x512 9.4 / 8.2, 8x384x128 with a folded
 //    LayerNorm 5.2 / 4.5), and encoder products beyond on 64x64 (4096x512x512 26.5 / 24.1,
 //    16384x1024x256 93.8 / 80.1): an fp32 k-step is bound by its MFMAs, so what counts is that
-//    the reads and loads stay behind them.
+//    the reads and loads stay behind them.  Short products to rows that no vector store takes stay
+//    on this file's (2600x32001x64 214 / 253, x128 297 / 310).
 int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role) {
   constexpr unsigned long long lim = 1ull << 32;
   const unsigned long long m = (unsigned long long)M + 256, n = (unsigned long long)N + 256;
@@ -775,7 +781,8 @@ int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role)
   const long long t32 = tiles(64, 32);
   if (role != 2 && !epi.wscale && t32 <= (epi.ctl ? 1200 : 512))
     return role == 0 && t32 > 256 && K <= (dt == DT::F32 ? 64 : 256) ? 0 : 32;
-  if (dt == DT::F32) return role == 0 ? 64 : 0;
+  const bool vec = (size_t)epi.ldc * (epi.out_f32 ? 4 : dt_bytes(dt)) % 16 == 0;
+  if (dt == DT::F32) return role == 0 && (vec || K > 128) ? 64 : 0;
   if (K % 128 != 0) return 0;
   if (role == 2) return epi.wscale || epi.lnf_colsum ? 0 : 128;
   const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t256 = tiles(256, 256);
@@ -784,9 +791,9 @@ int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role)
     return t128 >= (role == 1 && !epi.lnf_colsum ? 64 : 144) ? 128 : 0;
   }
   if (epi.lnf_colsum) return (t128 + 511) / 512 < (t64 + 767) / 768 ? 128 : 64;
-  if (t64 <= 256) return 64;
+  if (t64 <= (N % 128 != 0 && K <= 1024 ? 512 : 256)) return 64;
   const long long rounds = (t256 + 255) / 256;
-  return role == 0 && t256 * 10 >= rounds * 256 * 9 ? 256 : 128;
+  return role == 0 && t256 * 10 >= rounds * 256 * 9 && (vec || K > 256) ? 256 : 128;
 }
 
 hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int K, const GemmEpi& epi,

@@ -117,7 +117,8 @@ hipError_t gemm(DT dt, const void* A, int lda, const void* Bt, int M, int N, int
                 hipStream_t s, int role = 0, int tile = 0);
 
 // What gemm() with tile 0 runs a product on: 32, 64, 128 or 256 for a phased tile (below), 0 for
-// the tiles listed above.  Host only; of epi it reads ctl, wscale and lnf_colsum.
+// the tiles listed above.  Host only; of epi it reads ctl, wscale, lnf_colsum,
+// ldc and out_f32.
 int gemm_rows(DT dt, int lda, int M, int N, int K, const GemmEpi& epi, int role);
 
 // The same product on the phased tiles (nt_gemm_phased.h), bm = 32: 64x32 output

@@ -1886,13 +1886,16 @@ nt_status nt_op_gemm_ln(int32_t dtype, const void* d_A, int32_t lda, const void*
   return NT_OK;
 }
 
-int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8) {
+int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8,
+                        int32_t out_f32) {
   if (dtype < NT_F32 || dtype > NT_BF16 || (f8 && dtype != NT_F16)) return -1;
   if (M < 0 || N <= 0 || K <= 0 || K % 64 != 0 || lda < K) return -1;
   const float used = 0.f;   // only whether a pointer is set counts
   nt::GemmEpi e{};
   if (f8) e.wscale = &used;
   if (ln) e.lnf_colsum = &used;
+  e.ldc = N;
+  e.out_f32 = out_f32 ? 1 : 0;
   return nt::gemm_rows(static_cast<DT>(dtype), lda, M, N, K, e, ln ? 1 : 0);
 }
 

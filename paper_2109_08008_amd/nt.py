@@ -108,7 +108,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                  c_int32, P, P]),
         "nt_op_gemm_ln": (c_int32, [c_int32, P, c_int32, P, c_int32, c_int32, c_int32, P, c_float, P, P, c_int32,
                                     c_int32, c_int32, P, P]),
-        "nt_op_gemm_rows": (c_int32, [c_int32] * 7),
+        "nt_op_gemm_rows": (c_int32, [c_int32] * 8),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)
@@ -277,8 +277,9 @@ def nt_op_gemm_ln(dtype: str, d_A: int, lda: int, d_Bt: int, M: int, N: int, K: 
                                         tile, c_void_p(d_bscale) if d_bscale else None, _stream(stream)))
 
 
-def nt_op_gemm_rows(dtype: str, M: int, N: int, K: int, ln: bool = False, f8: bool = False, lda: int = 0) -> int:
-    return load_library().nt_op_gemm_rows(DTYPES[dtype], lda or K, M, N, K, int(ln), int(f8))
+def nt_op_gemm_rows(dtype: str, M: int, N: int, K: int, ln: bool = False, f8: bool = False, out_f32: bool = False,
+                    lda: int = 0) -> int:
+    return load_library().nt_op_gemm_rows(DTYPES[dtype], lda or K, M, N, K, int(ln), int(f8), int(out_f32))
 
 
 def nt_quantize_fp8(w: np.ndarray):

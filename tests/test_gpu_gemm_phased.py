@@ -58,8 +58,14 @@ PROJ = [
     (1089, 1024, 192, 0, 0, 64),        # an odd number of k-steps
     (2176, 1024, 384, 128, 0, 64),      # FP8: the last size on the older tiles
     (2177, 1024, 384, 128, 128, 64),    # one row in the last tile
-    (4095, 1000, 512, 128, 128, 64),    # 128x128, N ending inside a tile
+    (4095, 1000, 512, 64, 128, 64),     # N ending inside a tile: 512 tiles of 64x128
+    (4097, 1000, 512, 128, 128, 64),    # 520
+    (2177, 1000, 1088, 0, 0, 64),       # an odd number of k-steps again
+    (2177, 1000, 1152, 128, 128, 64),   # N ending inside a tile, a long k-loop
     (4225, 1031, 256, 128, 128, 64),    # 128x128, rows of 1031 elements: no vector access
+    (4225, 1031, 128, 128, 128, 0),     # fp32 rows that no vector store takes, a short k-loop
+    (4081, 4091, 256, 128, 128, 64),    # 256x256 but for its rows
+    (4081, 4091, 384, 256, 128, 64),    # 256x256 in spite of its rows
     (4097, 4096, 256, 128, 128, 64),    # 128x128 where 256x256 would leave a round nearly empty
     (4096, 4096, 128, 256, 128, 64),    # 256x256, whole tiles
     (4081, 4092, 640, 256, 128, 64),    # 256x256, ragged in both directions
