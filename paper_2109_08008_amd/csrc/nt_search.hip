@@ -295,7 +295,7 @@ __device__ __forceinline__ void list_insert(float (&v)[K2], int (&ix)[K2], float
 
 // Beam selection over stored logits: one workgroup a row, which it streams once.  HBM bounds
 // it (V * 4 bytes a row), so a thread keeps nothing of what it reads but its maximum and its
-// sum of exponentials: 43 registers, eight workgroups a CU, whose loads fill each other's
+// sum of exponentials: 48 registers, eight workgroups a CU, whose loads fill each other's
 // reductions.  The maxima of 64 quads of threads then give a threshold, their k2-th largest:
 // those quads hold k2 distinct logits at or above it, so the row's k2 best are at or above it
 // too.  Only the few threads whose maximum reaches it have candidates; their logits are read
@@ -304,8 +304,8 @@ __device__ __forceinline__ void list_insert(float (&v)[K2], int (&ix)[K2], float
 // SEL_CAP candidates (ties) is scanned again with sorted lists in each lane.  Any V and
 // alignment: single loads up to a 16-byte boundary and past the last vector.
 // k2 = 8, before (the row held in registers and sorted lists for V % 4 == 0 up to 32768, else
-// lists alone) and now: 1300 rows of 32000 57.2 -> 38.1 us (4.4 TB/s; a copy reaches 4.8), of
-// 32001 111 -> 40 us, 4000 rows 137 -> 99 us, 1 row 18.5 -> 9.1 us.  1024 threads a row
+// lists alone) and now: 1300 rows of 32000 57.2 -> 38.0 us (4.4 TB/s; a copy reaches 4.8), of
+// 32001 111 -> 40 us, 4000 rows 137 -> 99 us, 1 row 18.5 -> 8.7 us.  1024 threads a row
 // instead of 256: 51 us at 1300 rows and no gain at 1.
 constexpr int SEL_CAP = 512;
 
@@ -338,14 +338,20 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
                                                                   float* __restrict__ lse_out) {
   constexpr int NT = SEL_THREADS, NW = NT / kWave;
   static_assert(NT == 4 * 64 && NW * K2 <= SEL_CAP, "groups are quads; the candidate list holds every wave's best");
-  __shared__ float sm[NW], ss[NW], cand_v[SEL_CAP];
+  __shared__ float sm[NW], ss[NW];
+  __shared__ __attribute__((aligned(16))) float cand_v[SEL_CAP];
   __shared__ float4 gmax[16];
-  __shared__ int cand_i[SEL_CAP], cnt;
+  __shared__ __attribute__((aligned(16))) int cand_i[SEL_CAP];
+  __shared__ int cnt;
   const int r = blockIdx.x;
   if (ctl && r >= ctl[CTL_NLIVE] * beam) return;
   const float* x = logits + (size_t)r * V;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   if (tid == 0) cnt = 0;
+  for (int e = tid; e < SEL_CAP; e += NT) {
+    cand_v[e] = -INFINITY;
+    cand_i[e] = INT_MAX;
+  }
   // the row as `head` single logits up to a 16-byte boundary, nv vectors and a tail; threads
   // 0..3 take the head's, 4..7 the tail's
   const int head = min(V, (int)((16 - (reinterpret_cast<uintptr_t>(x) & 15)) & 15) / 4);
@@ -358,6 +364,7 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
     m = fmaxf(c, -INFINITY);
     sum = c == -INFINITY ? 0.f : __expf(c - c);   // 1; NaN of an infinity or a NaN
   }
+  float4 first = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
   for (int i0 = tid; i0 < nv; i0 += NT * SEL_BATCH) {
     float4 q[SEL_BATCH];
 #pragma unroll
@@ -365,6 +372,7 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
       const int i = i0 + u * NT;
       q[u] = i < nv ? x4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     }
+    if (i0 == tid) first = q[0];
     float mx = m;
 #pragma unroll
     for (int u = 0; u < SEL_BATCH; ++u) mx = fmaxf(mx, fmaxf(fmaxf(q[u].x, q[u].y), fmaxf(q[u].z, q[u].w)));
@@ -402,8 +410,26 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
       }
     }
   };
+  auto take4 = [&](float4 a, int i) {
+    take(a.x, head + 4 * i);
+    take(a.y, head + 4 * i + 1);
+    take(a.z, head + 4 * i + 2);
+    take(a.w, head + 4 * i + 3);
+  };
   if (single >= 0 && m >= thr) take(x[single], single);
   unsigned long long who = __ballot(m >= thr && m != -INFINITY);
+  // Each candidate thread goes through its own vectors where that takes no more turns than going
+  // through the threads: a short row, whose few groups give a low threshold or none (with the
+  // ranks counted four candidates a read, 64 rows of 101, k 8, 28.1 -> 9.8 us, of 500, k 32,
+  // 90 -> 33, of 1000, k 8, 7.8 -> 5.9).  Its first vector is still at hand.
+  const int own = (nv + NT - 1) / NT;
+  if (2 * own <= __popcll(who) + 1) {
+    if (who >> lane & 1) {
+      if (tid < nv) take4(first, tid);
+      for (int i = tid + NT; i < nv && *(volatile int*)&cnt <= SEL_CAP; i += NT) take4(x4[i], i);
+    }
+    who = 0;
+  }
   while (who && *(volatile int*)&cnt <= SEL_CAP) {
     // two of the wave's candidate threads at a time: lane u reads their vectors u, u + 64, ..
     const int l0 = __builtin_ctzll(who);
@@ -414,18 +440,8 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
       const int i0 = wave * kWave + l0 + u * NT, i1 = wave * kWave + l1 + u * NT;
       const bool h0 = i0 < nv, h1 = l1 >= 0 && i1 < nv;
       const float4 a = x4[h0 ? i0 : 0], b = x4[h1 ? i1 : 0];
-      if (h0) {
-        take(a.x, head + 4 * i0);
-        take(a.y, head + 4 * i0 + 1);
-        take(a.z, head + 4 * i0 + 2);
-        take(a.w, head + 4 * i0 + 3);
-      }
-      if (h1) {
-        take(b.x, head + 4 * i1);
-        take(b.y, head + 4 * i1 + 1);
-        take(b.z, head + 4 * i1 + 2);
-        take(b.w, head + 4 * i1 + 3);
-      }
+      if (h0) take4(a, i0);
+      if (h1) take4(b, i1);
     }
   }
   __syncthreads();
@@ -454,7 +470,11 @@ __global__ __launch_bounds__(SEL_THREADS) void beam_select_kernel(const float* _
     const float c = cand_v[e];
     const int i = cand_i[e];
     int at = 0;
-    for (int j = 0; j < n; ++j) at += better(cand_v[j], cand_i[j], c, i);
+    for (int j = 0; j < n; j += 4) {   // (entries past the last are empty, before no candidate)
+      const float4 v = *reinterpret_cast<const float4*>(cand_v + j);
+      const int4 w = *reinterpret_cast<const int4*>(cand_i + j);
+      at += better(v.x, w.x, c, i) + better(v.y, w.y, c, i) + better(v.z, w.z, c, i) + better(v.w, w.w, c, i);
+    }
     if (at < k2 && i != INT_MAX) {
       topv[at] = c;
       topi[at] = i;

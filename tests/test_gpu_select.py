@@ -80,7 +80,7 @@ def test_select_matches_numpy(V, kind, entry):
         assert np.array_equal(np.isfinite(ls), fin)
 
 
-@pytest.mark.parametrize("V", [1, 2, 3, 4, 5, 255, 1021, 1026, 2051, 8195])
+@pytest.mark.parametrize("V", [1, 2, 3, 4, 5, 33, 101, 255, 500, 1021, 1026, 2051, 8195])
 @pytest.mark.parametrize("kind", ["normal", "ties", "steps"])
 def test_select_stored_edges(V, kind):
     """The streamed row: heads and tails of 0 to 3 single logits (rows of odd V start at every
