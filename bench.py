@@ -48,55 +48,57 @@ GEMM_CLASSES = (0, 1, 2)
 # class) scaled by what the same counters read for a plain 512 MiB device copy (FETCH_SIZE
 # reads half the bytes moved, WRITE_SIZE all of them).  Valid only for the kernel source
 # the counters were taken on (sha256 over `files`); otherwise the bench reports null.
-GEMM_FILES = ["paper_2109_08008_amd/csrc/nt_gemm.hip", "paper_2109_08008_amd/csrc/nt_common.h"]
+GEMM_FILES = ["paper_2109_08008_amd/csrc/" + f for f in
+              ("nt_gemm.hip", "nt_gemm_common.h", "nt_gemm_phased.h", "nt_common.h")]
+GEMM_SHA256 = "ae988a98c7ef3c96267dcc98a2ea866293ec53072d7357bef9eba50719b39b16"
 TRAFFIC = {
-    ("gemm_dec", "wide-30-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 12662.90, "write_kib": 4063.62, "fetch_scale": 2.0, "write_scale": 1.0,
-    },
-    ("gemm_enc", "wide-30-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 111992.06, "write_kib": 74738.06, "fetch_scale": 2.0, "write_scale": 1.0,
-    },
-    ("gemm_vocab", "wide-30-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 44495.21, "write_kib": 5086.86, "fetch_scale": 2.0, "write_scale": 1.0,
+    ("gemm_enc", "base-6-6"): {
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 15739.96, "write_kib": 19820.73, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_dec", "base-6-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 3929.49, "write_kib": 1303.11, "fetch_scale": 2.0, "write_scale": 1.0,
-    },
-    ("gemm_enc", "base-6-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 15480.32, "write_kib": 19806.60, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 5195.25, "write_kib": 1303.11, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_vocab", "base-6-6"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 13998.60, "write_kib": 3141.33, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 13971.34, "write_kib": 3049.31, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_enc", "deep-shallow-greedy"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 15286.01, "write_kib": 17941.79, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 15375.65, "write_kib": 17963.41, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_dec", "deep-shallow-greedy"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 2063.13, "write_kib": 411.51, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 2095.18, "write_kib": 411.51, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_vocab", "deep-shallow-greedy"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 17058.90, "write_kib": 945.94, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 17008.21, "write_kib": 939.82, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_enc", "deep-shallow-beam"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 34254.48, "write_kib": 36548.84, "fetch_scale": 2.0, "write_scale": 1.0,
-    },
-    ("gemm_vocab", "deep-shallow-beam"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 22423.13, "write_kib": 6903.01, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 29739.48, "write_kib": 36666.91, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     ("gemm_dec", "deep-shallow-beam"): {
-        "files": GEMM_FILES, "sha256": "8696ca14961f0c4ac045848f028eeab73e938a62840b3e44679dde3faaf0af44",
-        "fetch_kib": 5920.51, "write_kib": 2873.06, "fetch_scale": 2.0, "write_scale": 1.0,
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 10117.48, "write_kib": 2873.11, "fetch_scale": 2.0, "write_scale": 1.0,
+    },
+    ("gemm_vocab", "deep-shallow-beam"): {
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 22397.31, "write_kib": 6768.20, "fetch_scale": 2.0, "write_scale": 1.0,
+    },
+    ("gemm_enc", "wide-30-6"): {
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 88129.00, "write_kib": 75663.37, "fetch_scale": 2.0, "write_scale": 1.0,
+    },
+    ("gemm_dec", "wide-30-6"): {
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 15227.16, "write_kib": 4064.38, "fetch_scale": 2.0, "write_scale": 1.0,
+    },
+    ("gemm_vocab", "wide-30-6"): {
+        "files": GEMM_FILES, "sha256": GEMM_SHA256,
+        "fetch_kib": 41389.72, "write_kib": 5962.40, "fetch_scale": 2.0, "write_scale": 1.0,
     },
 }
 
