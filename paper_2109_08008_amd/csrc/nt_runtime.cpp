@@ -1889,7 +1889,9 @@ nt_status nt_op_gemm_ln(int32_t dtype, const void* d_A, int32_t lda, const void*
 int32_t nt_op_gemm_rows(int32_t dtype, int32_t lda, int32_t M, int32_t N, int32_t K, int32_t ln, int32_t f8,
                         int32_t out_f32) {
   if (dtype < NT_F32 || dtype > NT_BF16 || (f8 && dtype != NT_F16)) return -1;
-  if (M < 0 || N <= 0 || K <= 0 || K % 64 != 0 || lda < K) return -1;
+  if (M < 0 || N <= 0 || K <= 0 || K % 64 != 0) return -1;
+  if (lda < K || (lda * (dtype == NT_F32 ? 4 : 2)) % 16 != 0) return -1;
+  if (out_f32 && ln) return -1;
   const float used = 0.f;   // only whether a pointer is set counts
   nt::GemmEpi e{};
   if (f8) e.wscale = &used;

@@ -215,7 +215,8 @@ def test_tiled_gemm_cases_reach_their_tiles(nt):
                     "f32": {(False, 0), (False, 32), (False, 64), (True, 0), (True, 32)}}
     # refused sizes and types; operands past 32-bit offsets
     for args, kw in ((("f16", 8, 8, 96), {}), (("f32", 8, 8, 64), {"f8": True}), (("f16", 8, 0, 64), {}),
-                     (("f16", 8, 8, 128), {"lda": 64})):
+                     (("f16", 8, 8, 128), {"lda": 64}), (("f16", 8, 8, 64), {"lda": 68}),
+                     (("f16", 8, 8, 64), {"ln": True, "out_f32": True})):
         assert nt.nt_op_gemm_rows(*args, **kw) == -1
     assert nt.nt_op_gemm_rows("f16", 1 << 20, 1024, 2048) == 0
     assert nt.nt_op_gemm_rows("f16", 1 << 20, 1024, 1024) == 256
